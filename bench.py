@@ -59,7 +59,7 @@ SWEEP_TRAFFIC_BYTES = (2.0 * 1603274 + 3200009) * 1024
 RUN_128 = dict(L=128, q=10, R=200000, K=501, beta_max=1.6, theta=20, seed=4)
 RUN_32 = dict(L=32, q=10, R=20000, K=401, beta_max=1.6, theta=10, seed=2)
 
-SWEEP_SYMBOL = "_ZN2pa12_GLOBAL__N_17k_sweepILj128ELj512ELb1ELb0EEEvNS_9SweepArgsE"
+SWEEP_SYMBOL = "_ZN2pa12_GLOBAL__N_112k_sweep_quadILj128ELj1024ELj2ELj16EEEvNS_9SweepArgsE"
 
 
 def linear_desc(pa, w, outputs=0):
@@ -86,7 +86,7 @@ def probe_class(op: str) -> str:
         return "perm"
     if op.startswith("v_sad"):
         return "sad"
-    if op.startswith("v_xad"):
+    if op.startswith(("v_xad", "v_add3", "v_dot4")):      # three-operand adders issue alike
         return "xad"
     if op.startswith("v_mul_hi"):
         return "mulhi"
@@ -98,9 +98,9 @@ def probe_class(op: str) -> str:
 def sweep_mix(lib_path: str, symbol: str = SWEEP_SYMBOL, attempts_per_iter: int = 32):
     """Vector instructions per attempt of the sweep's theta loop, by probe
     kind, read from the AMD assembly of the built library's gfx950 code object.  At
-    L = 128 with 512 lanes a lane updates 8 pairs per half-sweep, so one
-    iteration of the theta loop (both colours, fully unrolled) is 32 attempts
-    per lane."""
+    L = 128 with 1024 lanes a lane updates two quads of two replicas per
+    half-sweep, so one iteration of the theta loop (both colours, fully
+    unrolled) is 32 attempts per lane."""
     llvm = "/opt/rocm/llvm/bin"
     tmp = os.path.join(os.environ.get("TMPDIR", "/tmp"), f"pa_sweep_{os.getpid()}")
     try:
@@ -422,7 +422,7 @@ def main():
     achieved = ALG_OPS_PER_ATTEMPT * sweep_rate
     roofline = {
         "bound": "alu",
-        "kernel": "k_sweep",
+        "kernel": "k_sweep_quad",
         "achieved": achieved / 1e12,
         "peak": INT_OPS_PEAK / 1e12,
         "unit": "T int32 lane-ops/s",

@@ -186,7 +186,10 @@ pa_status pa_ctx_set_profiling(pa_ctx *ctx, int enable);
  * (a divisor of 64: several replicas per wave; a multiple of 64: one replica
  * per workgroup; neither, at L = 12, 20, 24: replicas spanning waves, several
  * per workgroup); results do not depend on the choice.  Other L use one
- * generic shape.  pa_ctx_get_lanes reports the lanes later runs will use and
+ * generic shape.  Sides divisible by 8 also have a kernel that updates four
+ * sites of a colour per lane (q <= 32, 32-bit thresholds); it runs with the
+ * lane counts it has, among them some that the tuned shapes below may name and
+ * pa_ctx_get_lanes does not list.  pa_ctx_get_lanes reports the lanes later runs will use and
  * the candidates (0 lanes and no candidates for the tiled path, L > 256);
  * pa_ctx_set_lanes picks one (0 = default) for later runs.
  * pa_autotune times every candidate on a synthetic population of about 64 MB

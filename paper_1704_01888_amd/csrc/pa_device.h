@@ -30,6 +30,7 @@ struct SweepArgs {
     uint32_t G;               // lanes per replica: a power of two up to 64 (several replicas
                               // per wave) or a multiple of 64 (one replica per workgroup)
     uint32_t waves_per_block;
+    uint32_t dword;           // 1: the dword kernel also where the quad kernel has the shape
 };
 
 // The resampling into step `step` of a population small enough for one
@@ -191,7 +192,7 @@ hipError_t launch_prep_batch(const PrepRec *recs, const uint32_t *start, uint32_
 
 // Batched forms: several runs per launch.  Sweep launches group runs of one
 // kernel class (sweep_class); `start` [n+1] gives each run's first workgroup.
-uint32_t sweep_class(uint32_t L, uint32_t q, bool t64, uint32_t G);
+uint32_t sweep_class(uint32_t L, uint32_t q, bool t64, uint32_t G, uint32_t nr = 0);
 void *sweep_kernel(uint32_t cls, bool batch);
 hipError_t launch_sweep_batch(uint32_t cls, const SweepArgs *runs, const uint32_t *start, uint32_t n,
                               uint32_t blocks, uint32_t threads, size_t lds, hipStream_t s);
@@ -256,6 +257,17 @@ void sweep_shape(uint32_t L, uint32_t lanes, uint32_t *G, uint32_t *waves_per_bl
 // q_counters: q when the sweep counts states for M~ (eq. (5)), else 0
 size_t sweep_lds_bytes(uint32_t N, uint32_t G, uint32_t waves_per_block, uint32_t q_counters);
 uint64_t replicas_per_block(uint32_t G, uint32_t waves_per_block);
+// Quad kernel (pa_quad.h): the most replicas per lane it has for a run's shape
+// (0: the run does not take it), its lane counts for L (up to 2), whether only
+// it has the shape.
+uint32_t quad_max_nr(uint32_t L, uint32_t q, bool t64, uint32_t G, uint32_t waves_per_block);
+uint32_t quad_lanes(uint32_t L, uint32_t *out);
+bool quad_only(uint32_t L, uint32_t G, uint32_t waves_per_block);
+size_t quad_lds_bytes(uint32_t N, uint32_t G, uint32_t waves_per_block, uint32_t nr, uint32_t q,
+                      uint32_t q_counters);
+struct SweepLaunch { uint32_t cls, blocks; uint64_t per_block; size_t lds; };
+uint32_t settle_sweep(SweepArgs &a, uint64_t replicas);
+SweepLaunch sweep_launch(const SweepArgs &a, uint32_t nr);
 // index of L in the table of lattices with lane choices (-1: none), and its size
 int lane_choice_index(uint32_t L);
 constexpr int LANE_CHOICE_COUNT = 13;

@@ -413,6 +413,7 @@ struct pa_run_state {
     uint64_t R_cur, R_prev;
     uint64_t r_dirty[2];  // extent of nonzero copy counts in each parity buffer
     uint32_t G, wpb;     // sweep shape: lanes per replica, waves per workgroup
+    bool dword;          // loaded spins beyond the quad kernel's: it is not used
     double mbF0;
     uint32_t first_step;  // step of the initial or loaded population
     uint64_t R_first;
@@ -555,6 +556,7 @@ pa::SweepArgs sweep_args(pa_run_state *r, uint32_t i, uint32_t mode, const uint8
     a.key1 = (uint32_t)(p.desc.seed >> 32);
     a.G = r->G;
     a.waves_per_block = r->wpb;
+    a.dword = r->dword ? 1u : 0u;
     return a;
 }
 
@@ -999,6 +1001,12 @@ static std::vector<std::pair<uint32_t, uint32_t>> tune_candidates(uint32_t L, in
             for (uint32_t w = 1; w <= 16; w *= 2) add(G, w);
         }
     }
+    // shapes only the quad kernel has: workgroups of a multiple of four waves
+    uint32_t ql[4];
+    const uint32_t nq = (L & 7u) ? 0u : pa::quad_lanes(L, ql);
+    for (uint32_t c = 0; c < nq; ++c)
+        for (uint32_t w = 4; w <= 16; w += 4)
+            if ((64 * w) % ql[c] == 0 && pa::quad_only(L, ql[c], w)) out.push_back({ql[c], w});
     return out;
 }
 
@@ -1275,6 +1283,7 @@ pa_status begin_run(pa_ctx *ctx, const pa_run_desc *desc, void *d_ws, uint64_t w
     r->broken = false;
     r->G = 0;
     r->wpb = 0;
+    r->dword = false;
     if (!p.tiled) {
         // a lane count set on the context, else the tuned shape of this
         // class, else the default
@@ -1414,6 +1423,11 @@ pa_status pa_run_load(pa_run_state *r, uint32_t step, uint64_t R_cur, const uint
         return fail(PA_ERR_INVALID, "step or population size out of range");
     pa_status st;
     hipStream_t s = r->stream;
+    // the quad kernel compares spins of five bits; a population with others
+    // (states beyond q) keeps the dword kernel
+    uint8_t top = 0;
+    for (size_t i = 0, n = (size_t)R_cur * p.N; i < n; ++i) top = std::max(top, spins[i]);
+    r->dword = top >= p.desc.q;
     r->step = step;
     r->R_cur = R_cur;
     r->R_prev = R_cur;
@@ -1778,20 +1792,10 @@ StepLaunch build_step(const std::vector<pa_run_state *> &active, std::vector<uin
     std::vector<uint32_t> sstart, mstart;
     std::vector<pa::SlotmapArgs> sm;
     std::vector<pa::PostArgs> po;
-    struct SW { uint32_t cls, blocks, threads; size_t lds; pa::SweepArgs a; };
+    struct SW { pa::SweepLaunch l; uint32_t threads; pa::SweepArgs a; };
     std::vector<SW> sw;
     uint32_t sblocks = 0, mblocks = 0;
-    auto add_sweep = [&](pa_run_state *r, const pa::SweepArgs &a) {
-        const Plan &p = r->plan;
-        const uint64_t per_block = pa::replicas_per_block(r->G, r->wpb);
-        SW e;
-        e.cls = pa::sweep_class(p.desc.L, p.desc.q, a.T[3] == 0, r->G);
-        e.blocks = (uint32_t)((r->R_cur + per_block - 1) / per_block);
-        e.threads = 64u * r->wpb;
-        e.lds = pa::sweep_lds_bytes(p.N, r->G, r->wpb, p.mag ? p.desc.q : 0u);
-        e.a = a;
-        sw.push_back(e);
-    };
+    auto add_sweep = [&](const pa::SweepArgs &a) { sw.push_back({pa::SweepLaunch{}, 0u, a}); };
     for (pa_run_state *r : active) {
         const Plan &p = r->plan;
         if (init) {
@@ -1799,7 +1803,7 @@ StepLaunch build_step(const std::vector<pa_run_state *> &active, std::vector<uin
             if (p.tiled)
                 L.tiled.push_back({tiled_args(r, 0, nullptr, nullptr, pop0), 0u, nullptr, true});
             else
-                add_sweep(r, sweep_args(r, 0, p.desc.init == PA_INIT_GROUND ? pa::SWEEP_INIT_GROUND
+                add_sweep(sweep_args(r, 0, p.desc.init == PA_INIT_GROUND ? pa::SWEEP_INIT_GROUND
                                                                             : pa::SWEEP_INIT_RANDOM,
                                         nullptr, nullptr, pop0, 0));
             po.push_back(post_args(r, 0));
@@ -1834,7 +1838,7 @@ StepLaunch build_step(const std::vector<pa_run_state *> &active, std::vector<uin
             po.push_back(post_args(r, g));
             continue;
         }
-        add_sweep(r, sweep_args(r, g, pa::SWEEP_UPDATE, r->at<uint8_t>(p.off_pop[prev_buf]), anc,
+        add_sweep(sweep_args(r, g, pa::SWEEP_UPDATE, r->at<uint8_t>(p.off_pop[prev_buf]), anc,
                                 r->at<uint8_t>(p.off_pop[new_buf]), p.desc.theta));
         r->cur = new_buf;
         r->step = g;
@@ -1855,21 +1859,32 @@ StepLaunch build_step(const std::vector<pa_run_state *> &active, std::vector<uin
     std::memcpy(blob.data() + L.sample_start_off, sstart.data(), sstart.size() * 4);
     std::memcpy(blob.data() + L.slot_off, sm.data(), sm.size() * sizeof(pa::SlotmapArgs));
     std::memcpy(blob.data() + L.slot_start_off, mstart.data(), mstart.size() * 4);
+    // the kernels, from all the replicas that runs of one shape bring
+    auto shape_key = [](const pa::SweepArgs &a) {
+        return ((uint64_t)pa::sweep_class(a.L, a.q, a.T[3] == 0, a.G) << 32) | ((uint64_t)(a.q <= 16) << 8) | a.waves_per_block;
+    };
+    std::map<uint64_t, uint64_t> replicas;
+    for (const SW &e : sw) replicas[shape_key(e.a)] += e.a.R_new;
+    for (SW &e : sw) {
+        const uint32_t nr = pa::settle_sweep(e.a, replicas[shape_key(e.a)]);
+        e.l = pa::sweep_launch(e.a, nr);
+        e.threads = 64u * e.a.waves_per_block;
+    }
     // sweep groups: runs of one kernel class contiguous in the table
     // (a class's runs may differ in waves per workgroup when tuned shapes
     // apply: a launch takes one block size)
     std::stable_sort(sw.begin(), sw.end(), [](const SW &x, const SW &y) {
-        return x.cls != y.cls ? x.cls < y.cls : x.threads < y.threads;
+        return x.l.cls != y.l.cls ? x.l.cls < y.l.cls : x.threads < y.threads;
     });
     L.sweep_off = take(n * sizeof(pa::SweepArgs));
     L.sweep_start_off = take(2 * (n + 1) * 4 + 4 * n);
     std::vector<uint32_t> starts;
     for (size_t k = 0; k < sw.size();) {
-        StepLaunch::Group G{sw[k].cls, (uint32_t)starts.size(), 0, 0, sw[k].threads, sw[k].lds};
-        while (k < sw.size() && sw[k].cls == G.cls && sw[k].threads == G.threads) {
-            G.lds = std::max(G.lds, sw[k].lds);   // runs of one class may differ in q and outputs
+        StepLaunch::Group G{sw[k].l.cls, (uint32_t)starts.size(), 0, 0, sw[k].threads, sw[k].l.lds};
+        while (k < sw.size() && sw[k].l.cls == G.cls && sw[k].threads == G.threads) {
+            G.lds = std::max(G.lds, sw[k].l.lds);   // runs of one class may differ in q and outputs
             starts.push_back(G.blocks);
-            G.blocks += sw[k].blocks;
+            G.blocks += sw[k].l.blocks;
             ++G.count;
             ++k;
         }

@@ -717,6 +717,8 @@ __global__ void __launch_bounds__(1024) k_sweep_batch(const SweepArgs *runs, con
     sweep_body<LT, GT, QSMALL, T64>(a, blockIdx.x - start[r], smem, threadIdx.x, blockDim.x, a.anc, 0u, a.R_new);
 }
 
+#include "pa_quad.h"
+
 // ---------------------------------------------------------------------------
 // Lattices with L = 2 (mod 4): a row of L bytes is not a whole number of
 // dwords, and a row holds L/2 sites of each colour, an odd number, so the two
@@ -2272,18 +2274,91 @@ size_t max_lds_per_block(int device) {
     return (size_t)v;
 }
 
-hipError_t launch_sweep(const SweepArgs &a, hipStream_t s) {
-    const uint64_t per_block = replicas_per_block(a.G, a.waves_per_block);
-    const uint64_t blocks = (a.R_new + per_block - 1) / per_block;
-    if (blocks == 0) return hipSuccess;
-    const size_t lds = sweep_lds_bytes(a.N, a.G, a.waves_per_block, a.Mt_out ? a.q : 0u);
-    void *kern = sweep_kernel(sweep_class(a.L, a.q, a.T[3] == 0, a.G), false);
-    if (lds > 65536) {
-        hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+// The quad kernel takes a shape (G, waves_per_block) where it has a
+// compile-time form of it: q <= 32 (five-bit spins), every 32-bit threshold.
+uint32_t quad_max_nr(uint32_t L, uint32_t q, bool t64, uint32_t G, uint32_t waves_per_block) {
+    if ((L & 7u) || L > 256 || q > 32 || t64 || (64u * waves_per_block) % G != 0) return 0;
+    return quad_shape(L, G).max_nr;
+}
+
+uint32_t quad_lanes(uint32_t L, uint32_t *out) {
+    uint32_t n = 0;
+    for (uint32_t G = 8; G <= 1024; G += 8)
+        if (quad_shape(L, G).max_nr) out[n++] = G;
+    return n;
+}
+
+uint64_t quad_replicas_per_block(uint32_t G, uint32_t waves_per_block, uint32_t nr) {
+    return (uint64_t)(64u * waves_per_block) / G * nr;
+}
+
+size_t quad_lds_bytes(uint32_t N, uint32_t G, uint32_t waves_per_block, uint32_t nr, uint32_t q,
+                      uint32_t q_counters) {
+    const uint32_t rpb = (uint32_t)quad_replicas_per_block(G, waves_per_block, nr);
+    return quad_tab_off(N, G, rpb, q_counters) + quad_tab_bytes(q);
+}
+
+// A shape only the quad kernel has: the dword kernel has no such lane count
+// for L, or holds one replica per workgroup with it.
+bool quad_only(uint32_t L, uint32_t G, uint32_t waves_per_block) {
+    if ((L & 7u) || L > 256 || quad_shape(L, G).max_nr == 0) return false;
+    uint32_t cand[2];
+    const uint32_t n = lane_candidates(L, cand);
+    bool dword = false;
+    for (uint32_t c = 0; c < n; ++c) dword = dword || cand[c] == G;
+    return !dword || (G > 64 && G % 64 == 0 && waves_per_block != G / 64);
+}
+
+uint32_t sweep_max_nr(const SweepArgs &a) {
+    return a.dword ? 0u : quad_max_nr(a.L, a.q, a.T[3] == 0, a.G, a.waves_per_block);
+}
+
+// Settles the kernel of a sweep in a launch that holds `replicas` of its class
+// in all and returns its replicas per lane (0: not the quad kernel).
+//   - A shape only the quad kernel has needs a launch of QUAD_MIN_WAVES, one
+//     round of the two 12-wave workgroups a compute unit holds: below it, and
+//     on a step the quad kernel does not take, the side's default shape is
+//     used (theta = 10, quads / default, attempts per ns: 24x24 766 / 887 with
+//     4000 waves and 1071 / 956 with 8000; 48x48 767 / 865 and 1062 / 984;
+//     96x96 767 / 891 and 1070 / 973).
+//   - Several replicas per lane leave fewer and longer waves, which pays from
+//     the shape's nr_waves on (see quad_shape).
+constexpr uint64_t QUAD_MIN_WAVES = 6144;
+uint32_t settle_sweep(SweepArgs &a, uint64_t replicas) {
+    uint32_t max_nr = sweep_max_nr(a);
+    if (quad_only(a.L, a.G, a.waves_per_block) && (max_nr == 0 || replicas * a.G / 64u < QUAD_MIN_WAVES)) {
+        sweep_shape(a.L, 0, &a.G, &a.waves_per_block);
+        max_nr = sweep_max_nr(a);
+    }
+    if (max_nr <= 1) return max_nr;
+    return replicas * a.G / 64u >= quad_shape(a.L, a.G).nr_waves ? max_nr : 1u;
+}
+
+// Launch shape of a sweep: its class, replicas per workgroup and LDS.  nr: the
+// replicas per lane of the quad kernel, 0 for the other kernels.
+SweepLaunch sweep_launch(const SweepArgs &a, uint32_t nr) {
+    SweepLaunch l;
+    const uint32_t qc = a.Mt_out ? a.q : 0u;
+    l.cls = sweep_class(a.L, a.q, a.T[3] == 0, a.G, nr);
+    l.per_block = nr ? quad_replicas_per_block(a.G, a.waves_per_block, nr)
+                     : replicas_per_block(a.G, a.waves_per_block);
+    l.lds = nr ? quad_lds_bytes(a.N, a.G, a.waves_per_block, nr, a.q, qc)
+               : sweep_lds_bytes(a.N, a.G, a.waves_per_block, qc);
+    l.blocks = (uint32_t)((a.R_new + l.per_block - 1) / l.per_block);
+    return l;
+}
+
+hipError_t launch_sweep(const SweepArgs &args, hipStream_t s) {
+    SweepArgs a = args;
+    const uint32_t nr = settle_sweep(a, a.R_new);
+    const SweepLaunch l = sweep_launch(a, nr);
+    if (l.blocks == 0) return hipSuccess;
+    void *kern = sweep_kernel(l.cls, false);
+    if (l.lds > 65536) {
+        hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)l.lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((void (*)(SweepArgs))kern, dim3((uint32_t)blocks), dim3(64u * a.waves_per_block), lds,
-                       s, a);
+    hipLaunchKernelGGL((void (*)(SweepArgs))kern, dim3(l.blocks), dim3(64u * a.waves_per_block), l.lds, s, a);
     return hipGetLastError();
 }
 
@@ -2300,17 +2375,39 @@ hipError_t launch_resample(const SampleArgs &a, const SlotmapArgs &m, hipStream_
 }
 
 // Kernel class: lattice side, lanes per replica, q <= 128, 64-bit thresholds;
-// bit 31 marks the byte kernel of L = 2 (mod 4).
-constexpr uint32_t CLASS_BYTES = 1u << 31;
-uint32_t sweep_class(uint32_t L, uint32_t q, bool t64, uint32_t G) {
+// bit 31 marks the byte kernel of L = 2 (mod 4), bit 30 the quad kernel with
+// log2 of its replicas per lane in bits 28-29 and q > 16 in bit 27.
+constexpr uint32_t CLASS_BYTES = 1u << 31, CLASS_QUAD = 1u << 30;
+uint32_t sweep_class(uint32_t L, uint32_t q, bool t64, uint32_t G, uint32_t nr) {
+    if (nr) return CLASS_QUAD | ((nr == 4 ? 2u : nr - 1u) << 28) | ((q > 16 ? 1u : 0u) << 27) | (L << 16) | (G << 2);
     if (L & 3u) return CLASS_BYTES | (L << 16);
     return (L << 16) | (G << 2) | ((q <= 128) ? 2u : 0u) | (t64 ? 1u : 0u);
+}
+
+// Quad kernels: every shape of quad_shape with one replica per lane and with
+// its largest number.
+static void *quad_kernel(uint32_t cls, bool batch) {
+    const uint32_t L = (cls >> 16) & 0x7FFu, G = (cls >> 2) & 0x3FFFu, nr = 1u << ((cls >> 28) & 3u);
+    const bool q32 = (cls >> 27) & 1u;
+#define PA_QUAD_NR(LV, GV, NV)                                                                                  \
+    if (L == LV && G == GV && nr == NV)                                                                         \
+        return batch ? (q32 ? (void *)k_sweep_quad_batch<LV, GV, NV, 32> : (void *)k_sweep_quad_batch<LV, GV, NV, 16>) \
+                     : (q32 ? (void *)k_sweep_quad<LV, GV, NV, 32> : (void *)k_sweep_quad<LV, GV, NV, 16>);
+#define PA_QUAD(LV, GV)                                                  \
+    static_assert(quad_shape(LV, GV).max_nr != 0, "a shape of the table"); \
+    PA_QUAD_NR(LV, GV, 1) PA_QUAD_NR(LV, GV, quad_shape(LV, GV).max_nr)
+    PA_QUAD(8, 8) PA_QUAD(16, 32) PA_QUAD(24, 24) PA_QUAD(32, 128) PA_QUAD(48, 96) PA_QUAD(64, 512)
+    PA_QUAD(96, 384) PA_QUAD(128, 1024) PA_QUAD(128, 512) PA_QUAD(192, 768) PA_QUAD(256, 1024)
+#undef PA_QUAD
+#undef PA_QUAD_NR
+    return nullptr;
 }
 
 // The instance for a class: fixed-shape when L is a power of two with a
 // candidate lane count and the 32-bit threshold form applies, else generic.
 void *sweep_kernel(uint32_t cls, bool batch) {
     if (cls & CLASS_BYTES) return batch ? (void *)k_sweep_bytes_batch : (void *)k_sweep_bytes;
+    if (cls & CLASS_QUAD) return quad_kernel(cls, batch);
     const uint32_t L = (cls >> 16) & 0x7FFFu, G = (cls >> 2) & 0x3FFFu;
     const bool qs = (cls & 2u) != 0, t64 = (cls & 1u) != 0;
 #define PA_INST(LV, GV)                                                                       \
@@ -2372,7 +2469,7 @@ hipError_t launch_resample_batch(const SampleArgs *sruns, const uint32_t *start,
 // Team kernels: the classes whose k_sweep workgroup (64 * waves_per_block
 // threads) divides 1024, with the 32-bit threshold form.
 void *team_kernel(uint32_t cls) {
-    if (cls & (CLASS_BYTES | 1u)) return nullptr;
+    if (cls & (CLASS_BYTES | CLASS_QUAD | 1u)) return nullptr;
     const uint32_t L = (cls >> 16) & 0x7FFFu, G = (cls >> 2) & 0x3FFFu;
     const bool qs = (cls & 2u) != 0;
 #define PA_TEAM(LV, GV) \

@@ -1,0 +1,97 @@
+"""The quad sweep kernel (q <= 32, four sites of one colour per dword) against
+the oracle, bit for bit: every shape it has, populations that leave the last
+lane group and workgroup partly idle, one and several replicas per lane, the
+edges of its q range (16, 17, 32 and, on the dword kernel, 33), steps whose
+thresholds need 64 bits in the middle of a run, and populations loaded with
+spins beyond its range."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1704_01888_amd as pa
+from paper_1704_01888_amd.workloads import linear_betas
+
+pytestmark = pytest.mark.gpu
+
+ALL = pa.OUT_FINAL | pa.OUT_HIST | pa.OUT_MAG | pa.OUT_DIGEST
+KEYS = ("R_i", "final_spins", "final_E", "last_anc", "hist", "Mt_sum", "mhist", "digest")
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = pa.Context(0)
+    yield c
+    c.close()
+
+
+def _check(ctx, **kw):
+    want = oracle.run(oracle.Desc(**kw), final=True, hist=True, magnetisation=True, digest=True)
+    got = pa.pa_run(ctx, pa.Desc(outputs=ALL, **kw))
+    for key in KEYS:
+        assert (got[key] == want[key]).all(), key
+    np.testing.assert_allclose(got["minus_beta_F"], want["minus_beta_F"], rtol=1e-12)
+
+
+# (L, lanes, waves per workgroup), replicas per lane in the larger population
+SHAPES = [(8, 8, 1), (8, 8, 4), (16, 32, 2), (16, 32, 16), (24, 24, 12), (32, 128, 2), (32, 128, 8), (48, 96, 12),
+          (64, 512, 8), (96, 384, 6), (96, 384, 12), (128, 512, 8), (128, 1024, 16), (192, 768, 12), (256, 1024, 16)]
+
+
+@pytest.mark.parametrize("L,G,w", SHAPES, ids=lambda v: str(v))
+def test_every_quad_shape_matches_the_oracle(ctx, L, G, w):
+    for r_class in range(4):
+        ctx.tune_set(L, 0, r_class, G, w)
+    small = max(3, 40000 // (L * L)) | 1
+    for n, q in enumerate((16, 17, 32, 2)):
+        print(f"\nL={L} lanes={G} waves={w} q={q} R={small + n}", flush=True)
+        _check(ctx, L=L, q=q, R=small + n, beta=linear_betas(1.7, 3), theta=2, seed=L + q, resample=0)
+
+
+@pytest.mark.parametrize("L,G,w,R", [(8, 8, 2, 131077), (16, 32, 2, 32771), (24, 24, 12, 21851), (32, 128, 2, 8195),
+                                     (48, 96, 12, 5463), (64, 512, 8, 2051), (96, 384, 12, 1367),
+                                     (128, 1024, 16, 513)], ids=lambda v: str(v))
+def test_several_replicas_per_lane_match_the_oracle(ctx, L, G, w, R):
+    for r_class in range(4):
+        ctx.tune_set(L, 0, r_class, G, w)
+    for q in (10, 20):
+        print(f"\nL={L} lanes={G} waves={w} q={q} R={R}", flush=True)
+        _check(ctx, L=L, q=q, R=R, beta=linear_betas(0.02, 2), theta=2, seed=L + q, resample=1)
+
+
+def test_steps_beyond_the_quad_kernel(ctx):
+    """q = 33, and beta up to 6, where the dE = 4 threshold is zero: the dword
+    kernels, also with a shape that only the quad kernel has."""
+    for L, G, w in ((24, 24, 12), (96, 384, 12), (64, 512, 8)):
+        for r_class in range(4):
+            ctx.tune_set(L, 0, r_class, G, w)
+        _check(ctx, L=L, q=33, R=21, beta=linear_betas(1.5, 3), theta=2, seed=5, resample=0)
+        _check(ctx, L=L, q=8, R=21, beta=linear_betas(6.0, 4), theta=2, seed=6, resample=0)
+
+
+def test_batch_of_quad_and_dword_runs(ctx):
+    runs = [dict(L=32, q=q, R=R, beta=linear_betas(1.2, 4), theta=2, seed=40 + q, resample=1)
+            for q, R in ((8, 5000), (10, 3001), (20, 700), (33, 300), (2, 1))]
+    runs += [dict(L=64, q=8, R=1500, beta=linear_betas(1.2, 6), theta=1, seed=50, resample=1),
+             dict(L=64, q=5, R=1501, beta=linear_betas(6.0, 5), theta=1, seed=51, resample=1)]
+    got = pa.pa_run_batch(ctx, [pa.Desc(outputs=ALL, **r) for r in runs])
+    for r, g in zip(runs, got):
+        want = oracle.run(oracle.Desc(**r), final=True, hist=True, magnetisation=True, digest=True)
+        for key in KEYS:
+            assert (g[key] == want[key]).all(), (key, r["q"], r["R"])
+
+
+def test_loaded_spins_beyond_q_keep_the_dword_kernel(ctx):
+    """Spins that no proposal makes (q and above) are states like any other to
+    the dword kernels, as before the quad kernel."""
+    kw = dict(L=32, q=4, R=64, beta=linear_betas(1.0, 4), theta=3, seed=9, resample=2)
+    rng = np.random.default_rng(1)
+    spins = rng.integers(0, 120, size=(64, 1024), dtype=np.uint8)
+    run = pa.Run(ctx, pa.Desc(**kw))
+    run.load(1, spins, 0.0)
+    run.advance(1)
+    got = run.read()
+    run.finish()
+    od = oracle.Desc(**kw)
+    for j in range(64):
+        want = oracle.sweep_replica(od, 2, j, spins[j])
+        assert (got["spins"][j] == want).all()

@@ -254,6 +254,8 @@ uint32_t lane_candidates(uint32_t L, uint32_t *out /*[2]*/);
 // Lanes per replica (log2) and waves per block for a lattice side L; `lanes`
 // selects a candidate (anything else: the default).
 void sweep_shape(uint32_t L, uint32_t lanes, uint32_t *G, uint32_t *waves_per_block);
+// The same for the dword, generic and byte kernels alone.
+void dword_shape(uint32_t L, uint32_t lanes, uint32_t *G, uint32_t *waves_per_block);
 // q_counters: q when the sweep counts states for M~ (eq. (5)), else 0
 size_t sweep_lds_bytes(uint32_t N, uint32_t G, uint32_t waves_per_block, uint32_t q_counters);
 uint64_t replicas_per_block(uint32_t G, uint32_t waves_per_block);
@@ -263,8 +265,8 @@ uint64_t replicas_per_block(uint32_t G, uint32_t waves_per_block);
 uint32_t quad_max_nr(uint32_t L, uint32_t q, bool t64, uint32_t G, uint32_t waves_per_block);
 uint32_t quad_lanes(uint32_t L, uint32_t *out);
 bool quad_only(uint32_t L, uint32_t G, uint32_t waves_per_block);
-size_t quad_lds_bytes(uint32_t N, uint32_t G, uint32_t waves_per_block, uint32_t nr, uint32_t q,
-                      uint32_t q_counters);
+// LDS of a workgroup of a shape, whichever kernel takes it.
+size_t shape_lds_bytes(uint32_t L, uint32_t q, uint32_t G, uint32_t waves_per_block, uint32_t q_counters);
 struct SweepLaunch { uint32_t cls, blocks; uint64_t per_block; size_t lds; };
 uint32_t settle_sweep(SweepArgs &a, uint64_t replicas);
 SweepLaunch sweep_launch(const SweepArgs &a, uint32_t nr);

@@ -977,6 +977,12 @@ static std::vector<std::pair<uint32_t, uint32_t>> tune_candidates(uint32_t L, in
     auto add = [&](uint32_t G, uint32_t w) {
         if (pa::sweep_lds_bytes(N, G, w, 0u) <= lds_max) out.push_back({G, w});
     };
+    // shapes only the quad kernel has: workgroups of a multiple of four waves
+    uint32_t ql[4];
+    const uint32_t nq = pa::quad_lanes(L, ql);
+    for (uint32_t c = 0; c < nq; ++c)
+        for (uint32_t w = 4; w <= 16; w += 4)
+            if (pa::quad_only(L, ql[c], w) && pa::quad_max_nr(L, 2, false, ql[c], w)) out.push_back({ql[c], w});
     if (L & 3u) {                                        // byte kernel: one replica per wave
         for (uint32_t w = 1; w <= 4; w *= 2) add(64, w);
         return out;
@@ -985,7 +991,7 @@ static std::vector<std::pair<uint32_t, uint32_t>> tune_candidates(uint32_t L, in
     uint32_t nc = pa::lane_candidates(L, cand);
     if (nc == 0) {                                       // the generic kernel's one lane count
         uint32_t G, w;
-        pa::sweep_shape(L, 0, &G, &w);
+        pa::dword_shape(L, 0, &G, &w);
         cand[0] = G;
         nc = 1;
     }
@@ -1001,12 +1007,6 @@ static std::vector<std::pair<uint32_t, uint32_t>> tune_candidates(uint32_t L, in
             for (uint32_t w = 1; w <= 16; w *= 2) add(G, w);
         }
     }
-    // shapes only the quad kernel has: workgroups of a multiple of four waves
-    uint32_t ql[4];
-    const uint32_t nq = (L & 7u) ? 0u : pa::quad_lanes(L, ql);
-    for (uint32_t c = 0; c < nq; ++c)
-        for (uint32_t w = 4; w <= 16; w += 4)
-            if ((64 * w) % ql[c] == 0 && pa::quad_only(L, ql[c], w)) out.push_back({ql[c], w});
     return out;
 }
 
@@ -1300,12 +1300,13 @@ pa_status begin_run(pa_ctx *ctx, const pa_run_desc *desc, void *d_ws, uint64_t w
                 tw = it->second.waves_per_block;
             }
         }
-        if (tG && pa::sweep_lds_bytes(p.N, tG, tw, p.mag ? p.desc.q : 0u) <= pa::max_lds_per_block(ctx->device)) {
+        if (tG && pa::shape_lds_bytes(p.desc.L, p.desc.q, tG, tw, p.mag ? p.desc.q : 0u) <=
+                      pa::max_lds_per_block(ctx->device)) {
             r->G = tG;
             r->wpb = tw;
         }
     }
-    if (!p.tiled && pa::sweep_lds_bytes(p.N, r->G, r->wpb, p.mag ? p.desc.q : 0u) >
+    if (!p.tiled && pa::shape_lds_bytes(p.desc.L, p.desc.q, r->G, r->wpb, p.mag ? p.desc.q : 0u) >
                         pa::max_lds_per_block(ctx->device)) {
         delete r;
         return fail(PA_ERR_UNSUPPORTED, "lattice does not fit the LDS of one workgroup on this device");

@@ -23,103 +23,11 @@
 // execute in order; a compiler fence keeps the half-sweeps apart); a replica
 // spread over several waves uses barriers.
 #include "pa_device.h"
+#include "pa_quad.h"
 
 namespace pa {
 
 namespace {
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-constexpr uint32_t PHILOX_M0 = 0xD2511F53u;
-constexpr uint32_t PHILOX_M1 = 0xCD9E8D57u;
-constexpr uint32_t PHILOX_W0 = 0x9E3779B9u;
-constexpr uint32_t PHILOX_W1 = 0xBB67AE85u;
-
-// Philox4x32-10 (Salmon et al., SC'11), all in registers.  The two xors of
-// each output word are one three-input bitop (truth table 0x96 = a ^ b ^ c).
-__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
-    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
-}
-
-// The truth table of a three-input bitop weighs its operands 0xF0, 0xCC, 0xAA.
-// Bitwise select m ? a : b.
-__device__ __forceinline__ uint32_t bit_select(uint32_t m, uint32_t a, uint32_t b) {
-    return __builtin_amdgcn_bitop3_b32(a, b, m, 0xE4);
-}
-
-// ~a & b.
-__device__ __forceinline__ uint32_t and_not(uint32_t a, uint32_t b) {
-    return __builtin_amdgcn_bitop3_b32(a, b, 0u, 0x0C);
-}
-
-// Rounds 2..10 of Philox after a first round whose product M0 * c0 is given.
-__device__ __forceinline__ uint4 philox_from(uint64_t p0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                             uint32_t k0, uint32_t k1) {
-    {
-        const uint64_t p1 = (uint64_t)PHILOX_M1 * c2;
-        const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0);
-        const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
-        c1 = (uint32_t)p1;
-        c3 = (uint32_t)p0;
-        uint32_t c0 = n0;
-        c2 = n2;
-        k0 += PHILOX_W0;
-        k1 += PHILOX_W1;
-#pragma unroll
-        for (int r = 1; r < 10; ++r) {
-            const uint64_t q0 = (uint64_t)PHILOX_M0 * c0;
-            const uint64_t q1 = (uint64_t)PHILOX_M1 * c2;
-            const uint32_t m0 = xor3((uint32_t)(q1 >> 32), c1, k0);
-            const uint32_t m2 = xor3((uint32_t)(q0 >> 32), c3, k1);
-            c1 = (uint32_t)q1;
-            c3 = (uint32_t)q0;
-            c0 = m0;
-            c2 = m2;
-            k0 += PHILOX_W0;
-            k1 += PHILOX_W1;
-        }
-        return make_uint4(c0, c1, c2, c3);
-    }
-}
-
-__device__ __forceinline__ uint4 philox(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                        uint32_t k0, uint32_t k1) {
-    return philox_from((uint64_t)PHILOX_M0 * c0, c1, c2, c3, k0, k1);
-}
-
-__device__ __forceinline__ uint64_t digest_term(uint32_t n, uint32_t k, uint32_t step, uint32_t d,
-                                                uint32_t key0, uint32_t key1) {
-    const uint4 w = philox(n, k, step, DOM_DIGEST << 28, key0, key1);
-    return ((((uint64_t)w.y << 32) | (uint64_t)w.x) | 1ull) * (uint64_t)d;
-}
-
-__device__ __forceinline__ uint32_t mulhi32(uint32_t w, uint32_t n) { return __umulhi(w, n); }
-
-// floor(w * n / 2^32) through the full 32x32->64 multiply: v_mad_u64_u32
-// issues at about twice the rate of v_mul_hi_u32 on gfx950, but the compiler
-// picks the latter when only the high half is used.
-__device__ __forceinline__ uint32_t mulhi32_wide(uint32_t w, uint32_t n) {
-    uint64_t prod, carry;
-    asm("v_mad_u64_u32 %0, %1, %2, %3, 0" : "=v"(prod), "=s"(carry) : "v"(w), "s"(n));
-    return (uint32_t)(prod >> 32);
-}
-
-__device__ __forceinline__ uint32_t perm(uint32_t hi, uint32_t lo, uint32_t sel) {
-    return __builtin_amdgcn_perm(hi, lo, sel);   // byte sel 0-3 from lo, 4-7 from hi
-}
-
-// Digest term of one dword of a replica: r * d mod 2^64, r the 64-bit word of
-// Philox(n, k, step, DIGEST) made odd (so any change of d changes the term).
-__device__ __forceinline__ uint64_t digest_term(uint32_t n, uint32_t k, uint32_t step, uint32_t d,
-                                                uint32_t key0, uint32_t key1);
-
-// Number of equal bytes between two words.
-__device__ __forceinline__ uint32_t eq_bytes(uint32_t a, uint32_t b) {
-    const uint32_t x = a ^ b;
-    const uint32_t nz = (((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x) & 0x80808080u;
-    return 4u - __popc(nz);
-}
 
 // LDS of the sweep and tiled workgroups: a 128-byte header (the 64-bit
 // thresholds, and the energy and digest sums of a multi-wave replica at bytes
@@ -303,70 +211,6 @@ __device__ __forceinline__ uint32_t update_pair(uint32_t D0, uint32_t Dx, uint32
     return bit_select(ps.mask, X, D0);
 }
 
-// Philox for the sweep counter (p, k, step, c3) with k, step, c3 and the key
-// wave-uniform: the first two rounds are half scalar.  P0 = M0 * p.
-struct SweepKey {
-    uint32_t n0, n1, c3k1, k0[10], k1[10];
-};
-
-__device__ __forceinline__ SweepKey sweep_key(uint32_t k, uint32_t step, uint32_t c3, uint32_t key0,
-                                              uint32_t key1) {
-    SweepKey s;
-    uint32_t a0 = key0, a1 = key1;
-#pragma unroll
-    for (int r = 0; r < 10; ++r) {
-        s.k0[r] = a0;
-        s.k1[r] = a1;
-        a0 += PHILOX_W0;
-        a1 += PHILOX_W1;
-    }
-    const uint64_t p1 = (uint64_t)PHILOX_M1 * step;
-    s.n0 = (uint32_t)(p1 >> 32) ^ k ^ key0;
-    s.n1 = (uint32_t)p1;
-    s.c3k1 = c3 ^ key1;
-    return s;
-}
-
-__device__ __forceinline__ uint4 philox_sweep(uint64_t P0, const SweepKey &s) {
-    // round 1
-    const uint32_t a2 = (uint32_t)(P0 >> 32) ^ s.c3k1;
-    const uint32_t a3 = (uint32_t)P0;
-    // round 2: M0 * n0 is uniform
-    const uint64_t q0 = (uint64_t)PHILOX_M0 * s.n0;
-    const uint64_t q1 = (uint64_t)PHILOX_M1 * a2;
-    uint32_t c0 = (uint32_t)(q1 >> 32) ^ (s.n1 ^ s.k0[1]);
-    uint32_t c1 = (uint32_t)q1;
-    uint32_t c2 = a3 ^ ((uint32_t)(q0 >> 32) ^ s.k1[1]);
-    uint32_t c3 = (uint32_t)q0;
-#pragma unroll
-    for (int r = 2; r < 10; ++r) {
-        const uint64_t r0 = (uint64_t)PHILOX_M0 * c0;
-        const uint64_t r1 = (uint64_t)PHILOX_M1 * c2;
-        const uint32_t m0 = xor3((uint32_t)(r1 >> 32), c1, s.k0[r]);
-        const uint32_t m2 = xor3((uint32_t)(r0 >> 32), c3, s.k1[r]);
-        c1 = (uint32_t)r1;
-        c3 = (uint32_t)r0;
-        c0 = m0;
-        c2 = m2;
-    }
-    return make_uint4(c0, c1, c2, c3);
-}
-
-__device__ __forceinline__ void wave_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-// Separates half-sweeps: within one wave LDS operations execute in order, so a
-// compiler fence suffices; a replica spread over several waves needs the
-// workgroup barrier.
-__device__ __forceinline__ void replica_fence(bool multiwave) {
-    if (multiwave) __syncthreads();
-    else wave_fence();
-}
-
-
-
 // Replica layout in LDS: rows -1 .. L of L bytes each; row r at byte (r+1)*L.
 // Rows -1 and L are copies of rows L-1 and 0 (periodic halo), kept current by
 // the lanes that update rows L-1 and 0.
@@ -471,35 +315,6 @@ __device__ __forceinline__ void sweeps_any(uint32_t *lds32, uint32_t g, uint32_t
             replica_fence(64u % G != 0u);
         }
     }
-}
-
-// f(i) for i = g, g + G, ... below n.  With the count and the stride known at
-// compile time (NC, GC != 0) the loop has a constant trip count, so that its
-// independent iterations (the loads of a gather) issue together.
-template <uint32_t NC, uint32_t GC, typename F>
-__device__ __forceinline__ void lane_stride(uint32_t g, uint32_t n, uint32_t G, F f) {
-    if constexpr (NC != 0 && GC != 0) {
-#pragma unroll
-        for (uint32_t c = 0; c < (NC + GC - 1) / GC; ++c) {
-            const uint32_t i = g + c * GC;
-            if (NC % GC == 0 || i < NC) f(i);
-        }
-    } else {
-        for (uint32_t i = g; i < n; i += G) f(i);
-    }
-}
-
-// Sum over the 64 lanes of a wave (all active), wave-uniform: four DPP adds
-// (quad_perm [1,0,3,2] and [2,3,0,1], row_ror 4 and 8) leave every lane of a
-// row of 16 with the row's sum; the four row sums are read from lanes 0, 16,
-// 32 and 48.
-__device__ __forceinline__ uint32_t wave_total(uint32_t v) {
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xF, 0xF, false);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, false);
-    return (uint32_t)(__builtin_amdgcn_readlane((int)v, 0) + __builtin_amdgcn_readlane((int)v, 16) +
-                      __builtin_amdgcn_readlane((int)v, 32) + __builtin_amdgcn_readlane((int)v, 48));
 }
 
 // One workgroup `block` of the sweep launch of one run (a): gather or create
@@ -689,22 +504,6 @@ __global__ void __launch_bounds__(1024) k_sweep(SweepArgs a) {
     sweep_body<LT, GT, QSMALL, T64>(a, blockIdx.x, smem, threadIdx.x, blockDim.x, a.anc, 0u, a.R_new);
 }
 
-// Index of the segment holding `block`: the last r < n with start[r] <= block
-// (start is non-decreasing from start[0] = 0, so segments without workgroups
-// are skipped).  Each wave counts the starts not after `block`, 64 per round
-// of vector loads, instead of following a chain of dependent loads through a
-// binary search; every thread of the workgroup must call it.
-__device__ __forceinline__ uint32_t segment_of(const uint32_t *start, uint32_t n, uint32_t block) {
-    const uint32_t lane = threadIdx.x & 63u;
-    uint32_t count = 0;
-    for (uint32_t i0 = 0; i0 < n; i0 += 64u) {
-        const uint32_t i = i0 + lane;
-        const bool before = i < n && start[i] <= block;
-        count += (uint32_t)__popcll(__ballot(before));
-    }
-    return __builtin_amdgcn_readfirstlane(count - 1u);
-}
-
 // Batched form: the workgroups of several runs' sweep launches (same lattice
 // class) in one launch; run r owns workgroups start[r] .. start[r+1]-1.
 template <uint32_t LT, uint32_t GT, bool QSMALL, bool T64>
@@ -716,8 +515,6 @@ __global__ void __launch_bounds__(1024) k_sweep_batch(const SweepArgs *runs, con
     extern __shared__ __align__(16) uint8_t smem[];
     sweep_body<LT, GT, QSMALL, T64>(a, blockIdx.x - start[r], smem, threadIdx.x, blockDim.x, a.anc, 0u, a.R_new);
 }
-
-#include "pa_quad.h"
 
 // ---------------------------------------------------------------------------
 // Lattices with L = 2 (mod 4): a row of L bytes is not a whole number of
@@ -2212,7 +2009,40 @@ uint32_t lane_candidates(uint32_t L, uint32_t *out) {
     return 2;
 }
 
+// quad_any, computed once per side.
+static const QuadAny &quad_any_shape(uint32_t L) {
+    struct Table {
+        QuadAny t[257];
+        Table() { for (uint32_t i = 0; i < 257; ++i) t[i] = quad_any(i); }
+    };
+    static const Table table;
+    return table.t[L <= 256 ? L : 0];
+}
+
+// The instances of the sides without lane choices are spread over translation
+// units (pa_quad_any.hip), by L / 2 mod 4.
+static void *quad_any_kernel(uint32_t L, bool batch) {
+    switch ((L / 2u) % 4u) {
+        case 0: return quad_any_part0(L, batch);
+        case 1: return quad_any_part1(L, batch);
+        case 2: return quad_any_part2(L, batch);
+        default: return quad_any_part3(L, batch);
+    }
+}
+
+// A side without lane choices that the quad kernel serves (quad_any).
+static bool quad_any_side(uint32_t L) { return lane_choice_index(L) < 0 && quad_any_shape(L).G != 0; }
+
 void sweep_shape(uint32_t L, uint32_t lanes, uint32_t *G_out, uint32_t *waves_per_block) {
+    if (quad_any_side(L)) {
+        *G_out = quad_any_shape(L).G;
+        *waves_per_block = quad_any_shape(L).waves;
+        return;
+    }
+    dword_shape(L, lanes, G_out, waves_per_block);
+}
+
+void dword_shape(uint32_t L, uint32_t lanes, uint32_t *G_out, uint32_t *waves_per_block) {
     uint32_t G = 0;
     if (L & 3u) {
         // byte kernel: one replica per wave, up to four per workgroup, as many
@@ -2277,7 +2107,10 @@ size_t max_lds_per_block(int device) {
 // The quad kernel takes a shape (G, waves_per_block) where it has a
 // compile-time form of it: q <= 32 (five-bit spins), every 32-bit threshold.
 uint32_t quad_max_nr(uint32_t L, uint32_t q, bool t64, uint32_t G, uint32_t waves_per_block) {
-    if ((L & 7u) || L > 256 || q > 32 || t64 || (64u * waves_per_block) % G != 0) return 0;
+    if (q > 32 || t64 || L > 256) return 0;
+    if (quad_any_side(L))
+        return G == quad_any_shape(L).G && 64u * waves_per_block >= G && waves_per_block <= quad_any_shape(L).waves ? 1u : 0u;
+    if ((64u * waves_per_block) % G != 0) return 0;
     return quad_shape(L, G).max_nr;
 }
 
@@ -2285,6 +2118,7 @@ uint32_t quad_lanes(uint32_t L, uint32_t *out) {
     uint32_t n = 0;
     for (uint32_t G = 8; G <= 1024; G += 8)
         if (quad_shape(L, G).max_nr) out[n++] = G;
+    if (quad_any_side(L)) out[n++] = quad_any_shape(L).G;
     return n;
 }
 
@@ -2292,21 +2126,37 @@ uint64_t quad_replicas_per_block(uint32_t G, uint32_t waves_per_block, uint32_t 
     return (uint64_t)(64u * waves_per_block) / G * nr;
 }
 
-size_t quad_lds_bytes(uint32_t N, uint32_t G, uint32_t waves_per_block, uint32_t nr, uint32_t q,
-                      uint32_t q_counters) {
+static size_t quad_lds_bytes(uint32_t L, uint32_t G, uint32_t waves_per_block, uint32_t nr, uint32_t q,
+                             uint32_t q_counters) {
     const uint32_t rpb = (uint32_t)quad_replicas_per_block(G, waves_per_block, nr);
-    return quad_tab_off(N, G, rpb, q_counters) + quad_tab_bytes(q);
+    return quad_tab_off(L, G, rpb, q_counters) + quad_tab_bytes(quad_any_side(L) ? 32u : q);
+}
+
+// The one lane count the generic or byte kernel has for a side without choices.
+static bool dword_lanes(uint32_t L, uint32_t G) {
+    uint32_t g, w;
+    dword_shape(L, 0, &g, &w);
+    return g == G;
 }
 
 // A shape only the quad kernel has: the dword kernel has no such lane count
 // for L, or holds one replica per workgroup with it.
 bool quad_only(uint32_t L, uint32_t G, uint32_t waves_per_block) {
-    if ((L & 7u) || L > 256 || quad_shape(L, G).max_nr == 0) return false;
+    if (L > 256) return false;
+    if (quad_any_side(L)) return G == quad_any_shape(L).G && waves_per_block != 0 && !dword_lanes(L, G);
+    if (quad_shape(L, G).max_nr == 0) return false;
     uint32_t cand[2];
     const uint32_t n = lane_candidates(L, cand);
     bool dword = false;
     for (uint32_t c = 0; c < n; ++c) dword = dword || cand[c] == G;
     return !dword || (G > 64 && G % 64 == 0 && waves_per_block != G / 64);
+}
+
+size_t shape_lds_bytes(uint32_t L, uint32_t q, uint32_t G, uint32_t waves_per_block, uint32_t q_counters) {
+    const uint32_t nr = quad_max_nr(L, q, false, G, waves_per_block);
+    if (nr) return quad_lds_bytes(L, G, waves_per_block, nr, q, q_counters);
+    if (quad_only(L, G, waves_per_block)) dword_shape(L, 0, &G, &waves_per_block);
+    return sweep_lds_bytes(L * L, G, waves_per_block, q_counters);
 }
 
 uint32_t sweep_max_nr(const SweepArgs &a) {
@@ -2315,18 +2165,31 @@ uint32_t sweep_max_nr(const SweepArgs &a) {
 
 // Settles the kernel of a sweep in a launch that holds `replicas` of its class
 // in all and returns its replicas per lane (0: not the quad kernel).
-//   - A shape only the quad kernel has needs a launch of QUAD_MIN_WAVES, one
-//     round of the two 12-wave workgroups a compute unit holds: below it, and
-//     on a step the quad kernel does not take, the side's default shape is
-//     used (theta = 10, quads / default, attempts per ns: 24x24 766 / 887 with
-//     4000 waves and 1071 / 956 with 8000; 48x48 767 / 865 and 1062 / 984;
-//     96x96 767 / 891 and 1070 / 973).
+//   - A step the quad kernel does not take, with a shape only it has: the
+//     dword kernel's default shape.
+//   - Sides with lane choices: such a shape needs a launch of QUAD_MIN_WAVES,
+//     one round of the two 12-wave workgroups a compute unit holds; below it
+//     the side's default shape is used (theta = 10, quads / default, attempts
+//     per ns: 24x24 766 / 887 with 4000 waves and 1071 / 956 with 8000; 48x48
+//     767 / 865 and 1062 / 984; 96x96 767 / 891 and 1070 / 973).
+//   - Other sides: workgroups of fewer waves until there are two per compute
+//     unit.
 //   - Several replicas per lane leave fewer and longer waves, which pays from
 //     the shape's nr_waves on (see quad_shape).
-constexpr uint64_t QUAD_MIN_WAVES = 6144;
+constexpr uint64_t QUAD_MIN_WAVES = 6144, QUAD_MIN_BLOCKS = 512;
 uint32_t settle_sweep(SweepArgs &a, uint64_t replicas) {
     uint32_t max_nr = sweep_max_nr(a);
-    if (quad_only(a.L, a.G, a.waves_per_block) && (max_nr == 0 || replicas * a.G / 64u < QUAD_MIN_WAVES)) {
+    if (max_nr == 0) {
+        if (quad_only(a.L, a.G, a.waves_per_block)) dword_shape(a.L, 0, &a.G, &a.waves_per_block);
+        return 0;
+    }
+    if (quad_any_side(a.L)) {
+        const uint32_t least = (a.G + 63u) / 64u;
+        while (a.waves_per_block > least && replicas < QUAD_MIN_BLOCKS * (64u * a.waves_per_block / a.G))
+            a.waves_per_block = a.waves_per_block >= least + 4u ? a.waves_per_block - 4u : least;
+        return max_nr;
+    }
+    if (quad_only(a.L, a.G, a.waves_per_block) && replicas * a.G / 64u < QUAD_MIN_WAVES) {
         sweep_shape(a.L, 0, &a.G, &a.waves_per_block);
         max_nr = sweep_max_nr(a);
     }
@@ -2342,7 +2205,7 @@ SweepLaunch sweep_launch(const SweepArgs &a, uint32_t nr) {
     l.cls = sweep_class(a.L, a.q, a.T[3] == 0, a.G, nr);
     l.per_block = nr ? quad_replicas_per_block(a.G, a.waves_per_block, nr)
                      : replicas_per_block(a.G, a.waves_per_block);
-    l.lds = nr ? quad_lds_bytes(a.N, a.G, a.waves_per_block, nr, a.q, qc)
+    l.lds = nr ? quad_lds_bytes(a.L, a.G, a.waves_per_block, nr, a.q, qc)
                : sweep_lds_bytes(a.N, a.G, a.waves_per_block, qc);
     l.blocks = (uint32_t)((a.R_new + l.per_block - 1) / l.per_block);
     return l;
@@ -2400,6 +2263,7 @@ static void *quad_kernel(uint32_t cls, bool batch) {
     PA_QUAD(96, 384) PA_QUAD(128, 1024) PA_QUAD(128, 512) PA_QUAD(192, 768) PA_QUAD(256, 1024)
 #undef PA_QUAD
 #undef PA_QUAD_NR
+    if (quad_any_side(L)) return quad_any_kernel(L, batch);
     return nullptr;
 }
 

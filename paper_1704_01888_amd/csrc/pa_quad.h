@@ -1,7 +1,7 @@
 // pa_quad.h -- the sweep of replicas held in LDS as two colour planes, four
 // sites of one colour per dword ("quads"): q <= 32, lattice sides with a
-// compile-time shape (quad_shape).  Part of pa_kernels.hip, which includes it
-// inside its namespaces after the helpers it uses.
+// compile-time shape (quad_shape) and, with a shape found by rule (quad_any),
+// every other even side from 8 to 254.
 //
 // What bounds it: the issue of vector integer instructions, like the dword
 // kernel (sweeps_fixed), so the layout is chosen to need fewer of them.
@@ -27,6 +27,12 @@
 // 64x64 1267 / 1422 / 1529, 96x96 1193 / 1386 / 1419, 128x128 (theta = 20)
 // 1290 / 1434 / 1475, 192x192 1139 / 1370, 256x256 1182 / 1280.
 #pragma once
+
+#include "pa_sweep.h"
+
+namespace pa {
+
+namespace {
 
 // Compile-time shape of the quads of lattice side L with G lanes per replica
 // (0: none): the largest NR, the waves per SIMD the registers are held to for
@@ -63,6 +69,64 @@ constexpr QuadShape quad_shape(uint32_t L, uint32_t G) {
     return {0, 0, 0, 0, false};
 }
 
+// How the rows of a side lie in a plane.  A row has H = L/2 sites of a colour in
+// DPQ dwords.  Quads never cross rows, and the pairs of sites that share a
+// Philox block (2m and 2m+1 of the colour's sites in row-major order) are
+// always the first or second half of one: where H is odd, an odd row starts at
+// a second site of a pair and its slots are shifted by one.  Slots outside
+// shift .. shift + H - 1 are padding: they hold some spin and are never read as
+// a neighbour.
+template <uint32_t L, uint32_t G>
+struct QuadGeo {
+    static constexpr uint32_t H = L / 2, ODD = H & 1u, DPQ = (H + ODD + 3u) / 4u;
+    static constexpr bool FULL = H % 4u == 0;                // no padding
+    static constexpr uint32_t RS = G / DPQ, J = (L + RS - 1) / RS;   // rows between a lane's quads, quads per lane
+    static constexpr uint32_t PLANE = L * DPQ, REP = 2 * PLANE;      // dwords of a plane and of a replica
+    static_assert(G % DPQ == 0 && RS <= L && (J == 1 || RS % 2 == 0), "shape");
+};
+__host__ __device__ constexpr uint32_t quad_rep_bytes(uint32_t L) { return 2u * L * 4u * ((L / 2u + ((L / 2u) & 1u) + 3u) / 4u); }
+
+// The shape of a side without a table entry: RS rows of lanes (even, so that a
+// lane's rows have one parity) and workgroups of 4, 8, 12 or 16 waves, chosen
+// for the largest share of lane time spent on sites (lanes beyond the last
+// whole replica, padding slots and rows past L are lost), less
+//   - 3 % for each quad per lane beyond the first, which make waves longer and
+//     fewer (50x50, 3001 / 30000 replicas, 8 waves, attempts per ns: 5 quads
+//     743 / 1040, 3 quads 877 / 1025), 5 % for a single one (no independent
+//     work: 950 at 30000),
+//   - 8 % and 12 % for workgroups of 12 and 16 waves, which wait longer at
+//     their barriers (100x100, 5003 / 30000 replicas: 16 waves 995 / 1175 with
+//     0.92 of the lane time, 8 waves 1053 / 1115 with 0.81),
+//   - 5 % beyond 6 quads per lane, where round 3's half is not kept,
+// and a part where the registers leave fewer than 24 waves on a compute unit.
+struct QuadAny { uint32_t G, waves, wpe; bool hoist; };
+constexpr QuadAny quad_any(uint32_t L) {
+    QuadAny best{0, 0, 0, false};
+    if (L < 8 || L > 254 || (L & 1u)) return best;
+    const uint32_t H = L / 2, DPQ = (H + (H & 1u) + 3) / 4;
+    double best_score = 0.0;
+    for (uint32_t w = 4; w <= 16; w += 4)
+        for (uint32_t RS = 2; RS <= L; RS += 2) {
+            const uint32_t G = RS * DPQ, J = (L + RS - 1) / RS;
+            if (G > 64 * w || J > 12) continue;
+            const bool hoist = J <= 6;
+            const uint32_t wpe = J <= 4 ? 8 : hoist ? 6 : 7;
+            const uint32_t reps = 64 * w / G, lds = reps * quad_rep_bytes(L) + 4096;
+            uint32_t blocks = 4 * wpe / w;
+            if (blocks * lds > 163840) blocks = 163840 / lds;
+            if (blocks == 0) continue;
+            const double share = (double)(reps * L * H) / (double)(64 * w * J * 4);
+            const double score = share * (J == 1 ? 0.95 : 1.0 - 0.03 * (J - 1)) *
+                                 (w == 16 ? 0.88 : w == 12 ? 0.92 : 1.0) * (hoist ? 1.0 : 0.95) *
+                                 (blocks * w >= 24 ? 1.0 : 0.6 + blocks * w / 60.0);
+            if (score > best_score + 1e-9) {
+                best_score = score;
+                best = QuadAny{G, w, wpe, hoist};
+            }
+        }
+    return best;
+}
+
 // Threshold table: entry (i0, i1), i = dE + 4 of two sites, holds both 32-bit
 // thresholds (as in load_thresholds) at byte UNIT * (i0 + 9 i1), UNIT the value
 // of a flag; the UNIT / 8 copies in the gaps serve the lanes in turn, which
@@ -70,12 +134,12 @@ constexpr QuadShape quad_shape(uint32_t L, uint32_t G) {
 __host__ __device__ constexpr uint32_t quad_unit(uint32_t q) { return q <= 16u ? 16u : 32u; }
 __host__ __device__ constexpr uint32_t quad_tab_bytes(uint32_t q) { return 81u * quad_unit(q); }
 
-// LDS of a workgroup: its replicas (N bytes each), the sums of replicas that
+// LDS of a workgroup: its replicas (quad_rep_bytes each), the sums of replicas that
 // are not inside one wave (digest 8 bytes, bonds and q_counters state counts
 // 4 bytes each per replica), the threshold table.
-__host__ __device__ inline uint32_t quad_tab_off(uint32_t N, uint32_t G, uint32_t rpb, uint32_t q_counters) {
+__host__ __device__ inline uint32_t quad_tab_off(uint32_t L, uint32_t G, uint32_t rpb, uint32_t q_counters) {
     const uint32_t sums = 64u % G != 0 ? rpb * (12u + 4u * q_counters) : 0u;
-    return (rpb * N + sums + 15u) & ~15u;
+    return (rpb * quad_rep_bytes(L) + sums + 15u) & ~15u;
 }
 
 // Rounds 1-2 of Philox and the half of round 3 that do not depend on the
@@ -114,12 +178,12 @@ __device__ __forceinline__ uint4 quad_rounds(const QuadPrefix &f, uint32_t r1_lo
 
 // Flags (UNIT per byte) of the unequal / equal bytes of a and b, all below UNIT.
 template <uint32_t UNIT>
-__device__ __forceinline__ uint32_t quad_ne(uint32_t a, uint32_t b) {
-    return ((a ^ b) + (UNIT - 1u) * 0x01010101u) & (UNIT * 0x01010101u);
+__device__ __forceinline__ uint32_t quad_ne(uint32_t a, uint32_t b, uint32_t mask = UNIT * 0x01010101u) {
+    return ((a ^ b) + (UNIT - 1u) * 0x01010101u) & mask;
 }
 template <uint32_t UNIT>
-__device__ __forceinline__ uint32_t quad_eq(uint32_t a, uint32_t b) {
-    return and_not((a ^ b) + (UNIT - 1u) * 0x01010101u, UNIT * 0x01010101u);
+__device__ __forceinline__ uint32_t quad_eq(uint32_t a, uint32_t b, uint32_t mask = UNIT * 0x01010101u) {
+    return and_not((a ^ b) + (UNIT - 1u) * 0x01010101u, mask);
 }
 
 // Metropolis update (proposal and acceptance as in the header comment of pa.h)
@@ -177,34 +241,53 @@ __device__ __forceinline__ uint32_t update_quad(uint32_t D, uint32_t N0, uint32_
     return D;
 }
 
-// theta sweeps of the NR replicas k[] at lds32 (N bytes each).  Quad qd =
-// g + j G of a lane is row qd / (L/8), dword qd mod (L/8) of a plane, and takes
-// Philox pairs 2 qd and 2 qd + 1.
-template <uint32_t LT, uint32_t GT, uint32_t NR, uint32_t UNIT>
-__device__ __forceinline__ void sweeps_quad(uint32_t *lds32, uint32_t g, const uint32_t (&k)[NR], const SweepArgs &a,
-                                            uint32_t base, uint32_t theta) {
-    constexpr uint32_t L = LT, N = L * L, DPQ = L / 8, G = GT, NQ = N / 8;
-    constexpr uint32_t PPQ = NQ / G, RS = G / DPQ;         // quads per lane, rows between them
-    constexpr uint32_t PLANE = L * DPQ, REP = 2 * PLANE;   // dwords of a plane and of a replica
-    constexpr bool HOIST = quad_shape(L, G).hoist;
-    static_assert(G % DPQ == 0 && NQ % G == 0 && (PPQ == 1 || RS % 2 == 0), "shape");
+// theta sweeps of the NR replicas k[] at lds32 (REP dwords each).  A lane's
+// quads are dword d of rows y0, y0 + RS, ... of a plane, dword index g + j G;
+// quad (y, d) takes Philox pairs floor(y H / 2) + 2d and the next.  `on`: a
+// lane of a replica (lanes beyond the last whole one only meet the barriers).
+template <uint32_t LT, uint32_t GT, uint32_t NR, uint32_t UNIT, bool HOIST>
+__device__ __forceinline__ void sweeps_quad(uint32_t *lds32, uint32_t g, bool on, const uint32_t (&k)[NR],
+                                            const SweepArgs &a, uint32_t base, uint32_t theta) {
+    using Geo = QuadGeo<LT, GT>;
+    constexpr uint32_t L = LT, G = GT, H = Geo::H, DPQ = Geo::DPQ, J = Geo::J, RS = Geo::RS;
+    constexpr uint32_t PLANE = Geo::PLANE, REP = Geo::REP;
     const uint32_t d = g % DPQ, y0 = g / DPQ;
-    const uint32_t left = d == 0 ? g + (DPQ - 1) : g - 1, right = d == DPQ - 1 ? g - (DPQ - 1) : g + 1;
+    const bool odd = (y0 & 1u) != 0;
+    const uint32_t sh = Geo::ODD && odd ? 1u : 0u;
+    // the horizontal neighbours that are not in the same dword of the other
+    // plane: to the left (dword left, bytes by sel_l) or to the right; the ends
+    // of a row meet (periodic)
+    const uint32_t last = (H - 1 + sh) / 4u, lb = (H - 1 + sh) % 4u;       // the last site's dword and byte
+    uint32_t left = g - 1, sel_l = 0x02010007u, right = g + 1, sel_r = 0x04030201u;
+    if (d == 0) {
+        left = g + last;
+        sel_l = sh ? 0x02010007u | ((4u + lb) << 8) : 0x02010000u | (4u + lb);
+    }
+    if (d == last) {
+        right = g - last;
+        sel_r = (sel_r & ~(0xFFu << (8u * lb))) | ((4u + sh) << (8u * lb));
+    }
     // the rows above the lane's first and below its last quad (periodic);
     // between them a neighbour is a row away
     const uint32_t up0 = y0 == 0 ? g + (L - 1) * DPQ : g - DPQ;
-    constexpr uint32_t LAST = (PPQ - 1) * G;
-    const uint32_t dn1 = y0 + (PPQ - 1) * RS == L - 1 ? d : g + LAST + DPQ;
-    const bool odd = (y0 & 1u) != 0;
+    constexpr uint32_t LAST = (J - 1) * G;
+    const uint32_t dn1 = y0 + (J - 1) * RS == L - 1 ? d : g + LAST + DPQ;
+    // where H is odd, those rows are shifted the other way: their neighbours
+    // reach into the next dword (even rows) or the one before
+    const uint32_t vs = !Geo::ODD ? 0u : sh ? (d == 0 ? 0u : ~0u) : (d == DPQ - 1 ? 0u : 1u);
+    const uint32_t sel_v = sh ? 0x02010007u : 0x04030201u;
+    const bool on_last = on && (L % RS == 0 || y0 + (J - 1) * RS < L);
     const uint32_t qm1 = a.q - 1u;
-    constexpr uint32_t PH = HOIST ? PPQ : 1, NH = HOIST ? NR : 1;
-    uint32_t hi[PPQ][2], r1_lo[PH][NH][2], r1k[PH][NH][2], c3k[NR], u2[NR];
-    const uint32_t lo0 = PHILOX_M0 * (2u * g);
+    constexpr uint32_t PH = HOIST ? J : 1, NH = HOIST ? NR : 1;
+    uint32_t hi[J][2], r1_lo[PH][NH][2], r1k[PH][NH][2], c3k[NR], u2[NR];
+    const uint32_t pair0 = ((y0 * H) >> 1) + 2u * d;
+    const uint32_t lo0 = PHILOX_M0 * pair0;
+    auto pair = [&](uint32_t j, uint32_t h) { return pair0 + j * (RS * H / 2u) + h; };
     const SweepKey key = sweep_key(0, a.step, 0, a.key0, a.key1);   // (k and c3 enter below)
 #pragma unroll
-    for (uint32_t j = 0; j < PPQ; ++j)
+    for (uint32_t j = 0; j < J; ++j)
 #pragma unroll
-        for (uint32_t h = 0; h < 2; ++h) hi[j][h] = (uint32_t)(((uint64_t)PHILOX_M0 * (2u * (g + j * G) + h)) >> 32);
+        for (uint32_t h = 0; h < 2; ++h) hi[j][h] = (uint32_t)(((uint64_t)PHILOX_M0 * pair(j, h)) >> 32);
 #pragma unroll
     for (uint32_t r = 0; r < NR; ++r) {
         const uint64_t q0 = (uint64_t)PHILOX_M0 * (key.n0 ^ k[r]);
@@ -212,10 +295,10 @@ __device__ __forceinline__ void sweeps_quad(uint32_t *lds32, uint32_t g, const u
         u2[r] = (uint32_t)(q0 >> 32) ^ key.k1[1];
         if constexpr (HOIST) {
 #pragma unroll
-            for (uint32_t j = 0; j < PPQ; ++j)
+            for (uint32_t j = 0; j < J; ++j)
 #pragma unroll
                 for (uint32_t h = 0; h < 2; ++h) {
-                    const uint64_t r1 = (uint64_t)PHILOX_M1 * ((PHILOX_M0 * (2u * (g + j * G) + h)) ^ u2[r]);
+                    const uint64_t r1 = (uint64_t)PHILOX_M1 * ((PHILOX_M0 * pair(j, h)) ^ u2[r]);
                     r1_lo[j][r][h] = (uint32_t)r1;
                     r1k[j][r][h] = (uint32_t)(r1 >> 32) ^ key.k0[2];
                 }
@@ -229,32 +312,39 @@ __device__ __forceinline__ void sweeps_quad(uint32_t *lds32, uint32_t g, const u
             // other plane holds their right neighbours and the shifted one,
             // from the dword to the left, their left ones; odd: the reverse
             const bool par = odd != (c != 0);
-            const uint32_t adj = par ? right : left, sel = par ? 0x04030201u : 0x02010007u;
-            const uint32_t po = c * PLANE, pp = PLANE - po;   // own and other plane
+            const uint32_t adj = par ? right : left, sel = par ? sel_r : sel_l;
+            constexpr uint32_t PO[2] = {0, PLANE};
+            const uint32_t po = PO[c], pp = PLANE - po;   // own and other plane
 #pragma unroll
-            for (uint32_t j = 0; j < PPQ; ++j) {
+            for (uint32_t j = 0; j < J; ++j) {
+                if (!(j == J - 1 ? on_last : on)) continue;
                 const QuadPrefix f0 = quad_prefix(hi[j][0], c3k1, key), f1 = quad_prefix(hi[j][1], c3k1, key);
 #pragma unroll
                 for (uint32_t r = 0; r < NR; ++r) {
                     uint32_t *own = lds32 + r * REP + po + j * G;
                     const uint32_t *opp = lds32 + r * REP + pp + j * G;
                     const uint32_t D = own[g], A = opp[g], Ax = opp[adj];
-                    const uint32_t U = j == 0 ? opp[up0] : (opp - DPQ)[g];
-                    const uint32_t Dn = j == PPQ - 1 ? (opp - LAST)[dn1] : (opp + DPQ)[g];
-                    uint32_t la, ka, lb, kb;
+                    const uint32_t *up = j == 0 ? opp + up0 : opp - DPQ + g;
+                    const uint32_t *dn = j == J - 1 ? opp - LAST + dn1 : opp + DPQ + g;
+                    uint32_t U = up[0], Dn = dn[0];
+                    if constexpr (Geo::ODD != 0) {
+                        U = perm(up[(int32_t)vs], U, sel_v);
+                        Dn = perm(dn[(int32_t)vs], Dn, sel_v);
+                    }
+                    uint32_t la, ka, lb1, kb;
                     if constexpr (HOIST) {
                         la = r1_lo[j][r][0]; ka = r1k[j][r][0];
-                        lb = r1_lo[j][r][1]; kb = r1k[j][r][1];
+                        lb1 = r1_lo[j][r][1]; kb = r1k[j][r][1];
                     } else {
-                        uint32_t lo = lo0 + PHILOX_M0 * (2u * j * G);
+                        uint32_t lo = lo0 + PHILOX_M0 * (j * (RS * H / 2u));
                         asm("" : "+v"(lo));        // recomputed per half-sweep, not kept
                         const uint64_t ra = (uint64_t)PHILOX_M1 * (lo ^ u2[r]);
                         const uint64_t rb = (uint64_t)PHILOX_M1 * ((lo + PHILOX_M0) ^ u2[r]);
                         la = (uint32_t)ra; ka = (uint32_t)(ra >> 32) ^ key.k0[2];
-                        lb = (uint32_t)rb; kb = (uint32_t)(rb >> 32) ^ key.k0[2];
+                        lb1 = (uint32_t)rb; kb = (uint32_t)(rb >> 32) ^ key.k0[2];
                     }
                     const uint4 wa = quad_rounds(f0, la, ka, c3k[r], key);
-                    const uint4 wb = quad_rounds(f1, lb, kb, c3k[r], key);
+                    const uint4 wb = quad_rounds(f1, lb1, kb, c3k[r], key);
                     own[g] = update_quad<UNIT>(D, perm(Ax, A, sel), A, U, Dn, wa, wb, qm1, base);
                 }
             }
@@ -263,28 +353,39 @@ __device__ __forceinline__ void sweeps_quad(uint32_t *lds32, uint32_t g, const u
     }
 }
 
+// Plane byte of site (y, x) of a replica.
+template <uint32_t L>
+__device__ __forceinline__ uint8_t *quad_site(uint8_t *rep, uint32_t y, uint32_t x) {
+    using Geo = QuadGeo<L, 2 * ((L / 2 + ((L / 2) & 1u) + 3) / 4)>;
+    const uint32_t sh = Geo::ODD ? (y & 1u) : 0u;
+    return rep + ((x + y) & 1u) * (4u * Geo::PLANE) + y * (4u * Geo::DPQ) + (x >> 1) + sh;
+}
+
 // One workgroup `block` of a quad sweep launch: gather or create its replicas,
 // theta sweeps, energies (and M~), store, as sweep_body does.  The workgroup
 // holds blockDim / G groups of G lanes, each NR replicas with consecutive
-// slots.
-template <uint32_t LT, uint32_t GT, uint32_t NR, uint32_t UNIT>
+// slots.  ANY: a side without a table entry (lanes may be left over).
+template <uint32_t LT, uint32_t GT, uint32_t NR, uint32_t UNIT, bool HOIST, bool ANY>
 __device__ __forceinline__ void sweep_quad_body(const SweepArgs &a, uint32_t block) {
     extern __shared__ __align__(16) uint8_t smem[];
-    constexpr uint32_t L = LT, N = L * L, G = GT, NQ = N / 8, HB = N / 2;   // HB: bytes of a plane
+    using Geo = QuadGeo<LT, GT>;
+    constexpr uint32_t L = LT, N = L * L, G = GT, DPQ = Geo::DPQ, PLANE = Geo::PLANE;
+    constexpr uint32_t REPB = 4 * Geo::REP, PB = 4 * PLANE;   // bytes of a replica and of a plane
     constexpr bool WAVE = 64u % G == 0;          // every replica inside one wave: no workgroup barriers
     const uint32_t tid = threadIdx.x, nthreads = blockDim.x;
     const uint32_t groups = nthreads / G, gi = tid / G, g = tid % G;
     const uint32_t rpb = groups * NR;
     const uint32_t qc = a.Mt_out ? a.q : 0u;
+    const bool on = !ANY || gi < groups;
 
     // sums of replicas spread over waves: digest [rpb] u64, bonds [rpb],
     // per-state counts [rpb][qc] u32
-    unsigned long long *acc_d = reinterpret_cast<unsigned long long *>(smem + rpb * N);
-    uint32_t *acc_e = reinterpret_cast<uint32_t *>(smem + rpb * N + 8u * rpb);
+    unsigned long long *acc_d = reinterpret_cast<unsigned long long *>(smem + rpb * REPB);
+    uint32_t *acc_e = reinterpret_cast<uint32_t *>(smem + rpb * REPB + 8u * rpb);
     uint32_t *acc_m = acc_e + rpb;
     if (!WAVE)
         for (uint32_t t = tid; t < rpb * (3u + qc); t += nthreads) reinterpret_cast<uint32_t *>(acc_d)[t] = 0u;
-    const uint32_t tab = quad_tab_off(N, G, rpb, qc);
+    const uint32_t tab = quad_tab_off(L, G, rpb, qc);
     for (uint32_t t = tid; t < 81u * (UNIT / 8u); t += nthreads) {
         const uint32_t e = t / (UNIT / 8u), i0 = e % 9u, i1 = e / 9u;
         const uint32_t x = i0 <= 4u ? 0xFFFFFFFFu : (uint32_t)(a.T[i0 - 5u] - 1u);
@@ -297,28 +398,65 @@ __device__ __forceinline__ void sweep_quad_body(const SweepArgs &a, uint32_t blo
 #pragma unroll
     for (uint32_t r = 0; r < NR; ++r)
         k[r] = G % 64u == 0 ? __builtin_amdgcn_readfirstlane((uint32_t)k0 + r) : (uint32_t)k0 + r;
-    auto live = [&](uint32_t r) { return k0 + r < a.R_new; };
-    uint8_t *rep0 = smem + (size_t)gi * NR * N;
+    auto live = [&](uint32_t r) { return on && k0 + r < a.R_new; };
+    uint8_t *rep0 = smem + (size_t)(on ? gi : 0u) * NR * REPB;
 
-    // ---- load or create the replicas: site (y, x) is byte x / 2 of row y of
-    // the plane of colour (x + y) mod 2
-    // W sites from x = W * (o mod L/W) of row o / (L/W) on, as even and odd bytes
-    constexpr uint32_t W = L % 16 == 0 ? 16 : 8;
+    // ---- load or create the replicas: site (y, x) is byte x / 2 (+ shift) of
+    // row y of the plane of colour (x + y) mod 2
+    // L a multiple of 8: W sites from x = W * (o mod L/W) of row o / (L/W) on, as
+    // their even and odd bytes
+    constexpr uint32_t W = L % 16 == 0 ? 16 : L % 8 == 0 ? 8 : 4;
     auto plane_even = [&](uint8_t *rep, uint32_t o) {     // the even-x bytes of chunk o
         const uint32_t y = o / (L / W);
-        return rep + (y & 1u) * HB + o * (W / 2);
+        return rep + (y & 1u) * PB + o * (W / 2);
     };
     auto plane_odd = [&](uint8_t *rep, uint32_t o) {
         const uint32_t y = o / (L / W);
-        return rep + (1u - (y & 1u)) * HB + o * (W / 2);
+        return rep + (1u - (y & 1u)) * PB + o * (W / 2);
     };
+    // other L: the four sites of dword o of the replica, two by two (a pair of
+    // sites x, x + 1 with x even never crosses a row)
+    auto sites2 = [&](uint8_t *rep, uint32_t m, uint8_t *&e, uint8_t *&o) {
+        const uint32_t y = m / Geo::H, x = 2u * (m % Geo::H);
+        e = quad_site<L>(rep, y, x);
+        o = quad_site<L>(rep, y, x + 1u);
+    };
+    auto put4 = [&](uint8_t *rep, uint32_t dd, uint32_t v) {
+#pragma unroll
+        for (uint32_t h = 0; h < 2; ++h) {
+            uint8_t *e, *o;
+            sites2(rep, 2u * dd + h, e, o);
+            *e = (uint8_t)(v >> (16u * h));
+            *o = (uint8_t)(v >> (16u * h + 8u));
+        }
+    };
+    auto get4 = [&](uint8_t *rep, uint32_t dd) {
+        uint32_t v = 0;
+#pragma unroll
+        for (uint32_t h = 0; h < 2; ++h) {
+            uint8_t *e, *o;
+            sites2(rep, 2u * dd + h, e, o);
+            v |= ((uint32_t)*e | ((uint32_t)*o << 8)) << (16u * h);
+        }
+        return v;
+    };
+    if constexpr (!Geo::FULL) {   // padding slots: some spin
+        if (on)
+            for (uint32_t o = g; o < 2u * L * NR; o += G) {
+                uint8_t *row = rep0 + o * (4u * DPQ);
+                const uint32_t sh = Geo::ODD ? ((o % L) & 1u) : 0u;
+                if (sh) row[0] = 0;
+                for (uint32_t i = sh + Geo::H; i < 4u * DPQ; ++i) row[i] = 0;
+            }
+    }
     if (a.mode == SWEEP_UPDATE) {
 #pragma unroll
         for (uint32_t r = 0; r < NR; ++r) {
-            uint8_t *rep = rep0 + r * N;
+            uint8_t *rep = rep0 + r * REPB;
             const bool in = live(r);
             const uint32_t src = in ? (a.anc ? a.anc[k[r]] : k[r]) : 0u;
             const uint8_t *gsrc = a.old_pop + (size_t)src * N;
+            if (on)
             lane_stride<N / W, G>(g, N / W, G, [&](uint32_t o) {
                 if constexpr (W == 16) {
                     const uint4 v = in ? reinterpret_cast<const uint4 *>(gsrc)[o] : make_uint4(0, 0, 0, 0);
@@ -326,33 +464,31 @@ __device__ __forceinline__ void sweep_quad_body(const SweepArgs &a, uint32_t blo
                         make_uint2(perm(v.y, v.x, 0x06040200u), perm(v.w, v.z, 0x06040200u));
                     *reinterpret_cast<uint2 *>(plane_odd(rep, o)) =
                         make_uint2(perm(v.y, v.x, 0x07050301u), perm(v.w, v.z, 0x07050301u));
-                } else {
+                } else if constexpr (W == 8) {
                     const uint2 v = in ? reinterpret_cast<const uint2 *>(gsrc)[o] : make_uint2(0, 0);
                     *reinterpret_cast<uint32_t *>(plane_even(rep, o)) = perm(v.y, v.x, 0x06040200u);
                     *reinterpret_cast<uint32_t *>(plane_odd(rep, o)) = perm(v.y, v.x, 0x07050301u);
+                } else {
+                    put4(rep, o, in ? reinterpret_cast<const uint32_t *>(gsrc)[o] : 0u);
                 }
             });
         }
-    } else {
+    } else if (on) {
 #pragma unroll
         for (uint32_t r = 0; r < NR; ++r) {
-            uint8_t *rep = rep0 + r * N;
+            uint8_t *rep = rep0 + r * REPB;
             if (a.mode == SWEEP_INIT_RANDOM) {
                 // site n takes word n mod 4 of Philox(n / 4, k, 0, INIT)
                 for (uint32_t dd = g; dd < N / 4u; dd += G) {
                     const uint4 w = philox(dd, k[r], 0u, DOM_INIT << 28, a.key0, a.key1);
-                    const uint32_t y = dd / (L / 4u);
-                    *reinterpret_cast<uint16_t *>(rep + (y & 1u) * HB + 2u * dd) =
-                        (uint16_t)(mulhi32(w.x, a.q) | (mulhi32(w.z, a.q) << 8));
-                    *reinterpret_cast<uint16_t *>(rep + (1u - (y & 1u)) * HB + 2u * dd) =
-                        (uint16_t)(mulhi32(w.y, a.q) | (mulhi32(w.w, a.q) << 8));
+                    put4(rep, dd, mulhi32(w.x, a.q) | (mulhi32(w.y, a.q) << 8) | (mulhi32(w.z, a.q) << 16) |
+                                      (mulhi32(w.w, a.q) << 24));
                 }
             } else {
                 // eq. (6): all spins alpha, alpha uniform over the q states
                 const uint4 w = philox(0u, k[r], 0u, DOM_GROUND << 28, a.key0, a.key1);
                 const uint32_t alpha = mulhi32(w.x, a.q) * 0x01010101u;
-                lane_stride<N / 4, G>(g, N / 4u, G,
-                                      [&](uint32_t dd) { reinterpret_cast<uint32_t *>(rep)[dd] = alpha; });
+                for (uint32_t dd = g; dd < Geo::REP; dd += G) reinterpret_cast<uint32_t *>(rep)[dd] = alpha;
             }
         }
     }
@@ -362,85 +498,136 @@ __device__ __forceinline__ void sweep_quad_body(const SweepArgs &a, uint32_t blo
     const uint32_t base = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t *)smem + tab +
                           8u * (tid % (UNIT / 8u));
     const uint32_t theta = a.mode == SWEEP_UPDATE ? a.theta : 0u;
-    sweeps_quad<L, G, NR, UNIT>(reinterpret_cast<uint32_t *>(rep0), g, k, a, base, theta);
+    sweeps_quad<L, G, NR, UNIT, HOIST>(reinterpret_cast<uint32_t *>(rep0), g, on, k, a, base, theta);
 
     // ---- energy (eq. (3)): every bond joins a colour-0 site to a neighbour
-    constexpr uint32_t DPQ = L / 8, PLANE = HB / 4;
-    auto group_sum = [&](uint32_t v) {           // over the group's lanes inside this wave
-        if constexpr (G % 64u == 0) return wave_total(v);
-        if constexpr (WAVE) {
+    auto group_sum = [&](uint32_t v) {           // over the lanes of a group inside one wave
 #pragma unroll
-            for (uint32_t off = G >> 1; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        }
-        return v;                                // (a group across waves: the lane's own)
+        for (uint32_t off = G >> 1; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        return v;
     };
-    const bool adds = G % 64u != 0 || (tid & 63u) == 0;      // lanes that add to a spread replica's sums
+    // v summed over the lanes of each group of this wave into at(group): whole
+    // waves of a group, or the two groups a wave of G > 64 lanes meets, by lane
+    // moves and one atomic each (64 atomics on one address serialise); small
+    // groups lane by lane.  Lanes left over count, with nothing, as the last group's.
+    const uint32_t gj = on ? gi : groups - 1u;
+    auto spread_add = [&](auto v, auto at) {
+        if (!on) v = 0;
+        if constexpr (G > 64u || G % 64u == 0) {
+            const uint32_t first = __builtin_amdgcn_readfirstlane(gj);
+            const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)gj, 63);
+            const auto own = wave_sum_all(gj == first ? v : decltype(v)(0));
+            if ((tid & 63u) == 0) atomicAdd(at(first), own);
+            if (G % 64u != 0 && end != first) {
+                const auto next = wave_sum_all(gj == first ? decltype(v)(0) : v);
+                if ((tid & 63u) == 0) atomicAdd(at(end), next);
+            }
+        } else if (on) {
+            atomicAdd(at(gi), v);
+        }
+    };
+    // flag mask of the slots of dword d of row y that hold sites
+    auto site_mask = [&](uint32_t y, uint32_t d) {
+        uint32_t m = UNIT * 0x01010101u;
+        if constexpr (!Geo::FULL) {
+            const uint32_t sh = Geo::ODD ? (y & 1u) : 0u;
+            if (sh && d == 0) m &= 0xFFFFFF00u;
+            if (4u * d + 4u > sh + Geo::H) m &= 0xFFFFFFFFu >> (8u * (4u * d + 4u - sh - Geo::H));
+        }
+        return m;
+    };
     uint32_t bonds[NR], mt[NR];
     uint64_t dig[NR];
 #pragma unroll
     for (uint32_t r = 0; r < NR; ++r) {
-        const uint32_t *p0 = reinterpret_cast<const uint32_t *>(rep0 + r * N), *p1 = p0 + PLANE;
-        const uint32_t li = gi * NR + r;
+        const uint32_t *p0 = reinterpret_cast<const uint32_t *>(rep0 + r * REPB), *p1 = p0 + PLANE;
         uint32_t ne = 0;
-        lane_stride<NQ, G>(g, NQ, G, [&](uint32_t qd) {
-            const uint32_t y = qd / DPQ, d = qd % DPQ;
+        if (on)
+        lane_stride<PLANE, G>(g, PLANE, G, [&](uint32_t qd) {
+            const uint32_t y = qd / DPQ, d = qd % DPQ, sh = Geo::ODD ? (y & 1u) : 0u;
+            const uint32_t last = (Geo::H - 1 + sh) / 4u, lb = (Geo::H - 1 + sh) % 4u;
             const uint32_t D = p0[qd], A = p1[qd];
-            const uint32_t Ax = p1[(y & 1u) ? (d == DPQ - 1 ? qd - (DPQ - 1) : qd + 1)
-                                            : (d == 0 ? qd + (DPQ - 1) : qd - 1)];
-            const uint32_t U = p1[y == 0 ? qd + (L - 1) * DPQ : qd - DPQ], Dn = p1[y == L - 1 ? d : qd + DPQ];
-            const uint32_t X = perm(Ax, A, (y & 1u) ? 0x04030201u : 0x02010007u);
-            ne = __builtin_amdgcn_sad_u8(quad_ne<UNIT>(D, A), 0u, ne);
-            ne = __builtin_amdgcn_sad_u8(quad_ne<UNIT>(D, X), 0u, ne);
-            ne = __builtin_amdgcn_sad_u8(quad_ne<UNIT>(D, U), 0u, ne);
-            ne = __builtin_amdgcn_sad_u8(quad_ne<UNIT>(D, Dn), 0u, ne);
+            uint32_t adj, sel;
+            if (y & 1u) {
+                adj = d == last ? qd - last : qd + 1;
+                sel = d == last ? (0x04030201u & ~(0xFFu << (8u * lb))) | ((4u + sh) << (8u * lb)) : 0x04030201u;
+            } else {             // (an even row has no shift)
+                adj = d == 0 ? qd + last : qd - 1;
+                sel = d == 0 ? 0x02010000u | (4u + lb) : 0x02010007u;
+            }
+            const uint32_t X = perm(p1[adj], A, sel);
+            const uint32_t up = y == 0 ? qd + (L - 1) * DPQ : qd - DPQ, dn = y == L - 1 ? d : qd + DPQ;
+            uint32_t U = p1[up], Dn = p1[dn];
+            if constexpr (Geo::ODD != 0) {
+                const uint32_t vs = sh ? (d == 0 ? 0u : ~0u) : (d == DPQ - 1 ? 0u : 1u);
+                const uint32_t sv = sh ? 0x02010007u : 0x04030201u;
+                U = perm(p1[up + vs], U, sv);
+                Dn = perm(p1[dn + vs], Dn, sv);
+            }
+            const uint32_t m = site_mask(y, d);
+            ne = __builtin_amdgcn_sad_u8(quad_ne<UNIT>(D, A, m), 0u, ne);
+            ne = __builtin_amdgcn_sad_u8(quad_ne<UNIT>(D, X, m), 0u, ne);
+            ne = __builtin_amdgcn_sad_u8(quad_ne<UNIT>(D, U, m), 0u, ne);
+            ne = __builtin_amdgcn_sad_u8(quad_ne<UNIT>(D, Dn, m), 0u, ne);
         });
-        bonds[r] = group_sum(ne / UNIT);         // unequal neighbours; 2N bonds less these are equal
-        if (!WAVE && adds) atomicAdd(&acc_e[li], bonds[r]);
+        bonds[r] = WAVE ? group_sum(ne / UNIT) : 0u;   // unequal neighbours; 2N bonds less these are equal
+        if (!WAVE) spread_add(ne / UNIT, [&](uint32_t q) { return &acc_e[q * NR + r]; });
         // ---- magnetisation (eq. (5)): the largest number of sites in one state
         mt[r] = 0;
-        if (a.Mt_out)
-            for (uint32_t st = 0; st < a.q; ++st) {
-                uint32_t c = 0;
-                lane_stride<N / 4, G>(g, N / 4u, G, [&](uint32_t dd) {
-                    c = __builtin_amdgcn_sad_u8(quad_eq<UNIT>(p0[dd], st * 0x01010101u), 0u, c);
+        if (a.Mt_out) {
+            // two states' counts share a word where N < 2^16
+            constexpr uint32_t PER = N < 65536u ? 2u : 1u;
+            for (uint32_t st = 0; st < a.q; st += PER) {
+                uint32_t c0 = 0, c1 = 0;
+                if (on)
+                lane_stride<Geo::REP, G>(g, Geo::REP, G, [&](uint32_t dd) {
+                    const uint32_t m = site_mask((dd / DPQ) % L, dd % DPQ);
+                    c0 = __builtin_amdgcn_sad_u8(quad_eq<UNIT>(p0[dd], st * 0x01010101u, m), 0u, c0);
+                    if (PER == 2u) c1 = __builtin_amdgcn_sad_u8(quad_eq<UNIT>(p0[dd], (st + 1u) * 0x01010101u, m), 0u, c1);
                 });
-                c = group_sum(c / UNIT);
-                if (WAVE) mt[r] = max(mt[r], c);
-                else if (adds) atomicAdd(&acc_m[li * qc + st], c);
+                const uint32_t c = c0 / UNIT | (c1 / UNIT) << 16;
+                if constexpr (WAVE) {
+                    const uint32_t w = group_sum(c);
+                    mt[r] = max(mt[r], max(w & 0xFFFFu, w >> 16));
+                } else {
+                    spread_add(c, [&](uint32_t q) { return &acc_m[(q * NR + r) * qc + st / PER]; });
+                }
             }
+        }
         // ---- digest term (order-free sum over the dwords of four sites of a row)
         dig[r] = 0;
         if (a.H_out) {
-            for (uint32_t dd = g; dd < N / 4u; dd += G) {
-                const uint8_t *rep = rep0 + r * N;
-                const uint32_t y = dd / (L / 4u);
-                const uint32_t e = *reinterpret_cast<const uint16_t *>(rep + (y & 1u) * HB + 2u * dd);
-                const uint32_t o = *reinterpret_cast<const uint16_t *>(rep + (1u - (y & 1u)) * HB + 2u * dd);
-                dig[r] += digest_term(dd, k[r], a.step, perm(o, e, 0x05010400u), a.key0, a.key1);
+            if (on)
+                for (uint32_t dd = g; dd < N / 4u; dd += G)
+                    dig[r] += digest_term(dd, k[r], a.step, get4(rep0 + r * REPB, dd), a.key0, a.key1);
+            if constexpr (WAVE) {
+                for (uint32_t off = G >> 1; off > 0; off >>= 1) dig[r] += __shfl_xor(dig[r], off, 64);
+            } else {
+                spread_add((unsigned long long)dig[r], [&](uint32_t q) { return &acc_d[q * NR + r]; });
             }
-            if constexpr (WAVE || G % 64u == 0)
-                for (uint32_t off = (G < 64u ? G : 64u) >> 1; off > 0; off >>= 1) dig[r] += __shfl_xor(dig[r], off, 64);
-            if (!WAVE && adds) atomicAdd(&acc_d[li], (unsigned long long)dig[r]);
         }
     }
     if (!WAVE) __syncthreads();
 #pragma unroll
     for (uint32_t r = 0; r < NR; ++r) {
         if (!live(r)) continue;
-        const uint32_t li = gi * NR + r;
-        if (!WAVE) {
-            bonds[r] = acc_e[li];
-            if (a.Mt_out)
-                for (uint32_t st = 0; st < a.q; ++st) mt[r] = max(mt[r], acc_m[li * qc + st]);
-            if (a.H_out) dig[r] = acc_d[li];
-        }
         if (g == 0) {
+            const uint32_t li = gi * NR + r;
+            if constexpr (!WAVE) {
+                bonds[r] = acc_e[li];
+                if (a.Mt_out)
+                    for (uint32_t st = 0; st < a.q; ++st) {
+                        const uint32_t w = acc_m[li * qc + (N < 65536u ? st / 2u : st)];
+                        mt[r] = max(mt[r], N < 65536u ? (w >> (16u * (st & 1u))) & 0xFFFFu : w);
+                    }
+                if (a.H_out) dig[r] = acc_d[li];
+            }
             a.E_out[k[r]] = (int32_t)bonds[r] - (int32_t)(2u * N);
             if (a.Mt_out) a.Mt_out[k[r]] = mt[r];
             if (a.H_out) a.H_out[k[r]] = dig[r];
         }
         // streaming stores, as in sweep_body
-        uint8_t *rep = rep0 + r * N;
+        uint8_t *rep = rep0 + r * REPB;
         uint8_t *gdst = a.new_pop + (size_t)k[r] * N;
         lane_stride<N / W, G>(g, N / W, G, [&](uint32_t o) {
             if constexpr (W == 16) {
@@ -449,11 +636,13 @@ __device__ __forceinline__ void sweep_quad_body(const SweepArgs &a, uint32_t blo
                 const u32x4 v = {perm(d.x, e.x, 0x05010400u), perm(d.x, e.x, 0x07030602u),
                                  perm(d.y, e.y, 0x05010400u), perm(d.y, e.y, 0x07030602u)};
                 __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(gdst) + o);
-            } else {
+            } else if constexpr (W == 8) {
                 const uint32_t e = *reinterpret_cast<const uint32_t *>(plane_even(rep, o));
                 const uint32_t d = *reinterpret_cast<const uint32_t *>(plane_odd(rep, o));
                 const u32x2 v = {perm(d, e, 0x05010400u), perm(d, e, 0x07030602u)};
                 __builtin_nontemporal_store(v, reinterpret_cast<u32x2 *>(gdst) + o);
+            } else {
+                __builtin_nontemporal_store(get4(rep, o), reinterpret_cast<uint32_t *>(gdst) + o);
             }
         });
     }
@@ -466,7 +655,7 @@ constexpr uint32_t quad_wpe(uint32_t L, uint32_t G, uint32_t NR) {
 template <uint32_t LT, uint32_t GT, uint32_t NR, uint32_t UNIT>
 __global__ void __attribute__((amdgpu_flat_work_group_size(64, 1024), amdgpu_waves_per_eu(quad_wpe(LT, GT, NR))))
 k_sweep_quad(SweepArgs a) {
-    sweep_quad_body<LT, GT, NR, UNIT>(a, blockIdx.x);
+    sweep_quad_body<LT, GT, NR, UNIT, quad_shape(LT, GT).hoist, false>(a, blockIdx.x);
 }
 
 // Batched form: run r owns workgroups start[r] .. start[r+1]-1.
@@ -475,5 +664,31 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(64, 1024), amdgpu_wav
 k_sweep_quad_batch(const SweepArgs *runs, const uint32_t *start, uint32_t n) {
     const uint32_t r = segment_of(start, n, blockIdx.x);
     const SweepArgs &a = runs[r];    // by reference: a copy would go to scratch memory
-    sweep_quad_body<LT, GT, NR, UNIT>(a, blockIdx.x - start[r]);
+    sweep_quad_body<LT, GT, NR, UNIT, quad_shape(LT, GT).hoist, false>(a, blockIdx.x - start[r]);
 }
+
+// The sides without a table entry (shape quad_any, 32 states).
+template <uint32_t LT>
+__global__ void __attribute__((amdgpu_flat_work_group_size(64, 64 * quad_any(LT).waves), amdgpu_waves_per_eu(quad_any(LT).wpe)))
+k_sweep_any(SweepArgs a) {
+    sweep_quad_body<LT, quad_any(LT).G, 1, 32, quad_any(LT).hoist, true>(a, blockIdx.x);
+}
+
+template <uint32_t LT>
+__global__ void __attribute__((amdgpu_flat_work_group_size(64, 64 * quad_any(LT).waves), amdgpu_waves_per_eu(quad_any(LT).wpe)))
+k_sweep_any_batch(const SweepArgs *runs, const uint32_t *start, uint32_t n) {
+    const uint32_t r = segment_of(start, n, blockIdx.x);
+    const SweepArgs &a = runs[r];
+    sweep_quad_body<LT, quad_any(LT).G, 1, 32, quad_any(LT).hoist, true>(a, blockIdx.x - start[r]);
+}
+
+}  // namespace
+
+// Kernels of the sides without a table entry (pa_quad_any.hip, one translation
+// unit each); null for a side of another part.
+void *quad_any_part0(uint32_t L, bool batch);
+void *quad_any_part1(uint32_t L, bool batch);
+void *quad_any_part2(uint32_t L, bool batch);
+void *quad_any_part3(uint32_t L, bool batch);
+
+}  // namespace pa

@@ -95,3 +95,25 @@ def test_loaded_spins_beyond_q_keep_the_dword_kernel(ctx):
     for j in range(64):
         want = oracle.sweep_replica(od, 2, j, spins[j])
         assert (got["spins"][j] == want).all()
+
+
+def _any_sides():
+    """Sides from 8 on without lane choices (L = 10, 14, 18, 22, 26, 28, ...):
+    a small one and a large one of every residue mod 8, and both ends."""
+    return [10, 14, 18, 22, 26, 28, 36, 40, 44, 50, 62, 100, 108, 118, 136, 152, 178, 206, 228, 248, 252, 254]
+
+
+@pytest.mark.parametrize("L", _any_sides())
+def test_sides_without_lane_choices_match_the_oracle(ctx, L):
+    """Whole and partly idle workgroups, and the smaller workgroups of a small
+    launch; the byte and generic kernels of q = 33 on the same side."""
+    assert ctx.get_lanes(L)[1] == []
+    big = 1200 if L < 40 else max(3, 3000000 // (L * L))
+    for q, R in ((3, 5), (16, big), (32, big | 1), (33, 7)):
+        print(f"\nL={L} q={q} R={R}", flush=True)
+        _check(ctx, L=L, q=q, R=R, beta=linear_betas(1.5, 2), theta=2, seed=L + q, resample=1)
+
+
+def test_side_without_lane_choices_from_ground_states_to_64_bit_thresholds(ctx):
+    for L in (18, 36, 50):
+        _check(ctx, L=L, q=6, R=40, beta=np.array([6.0, 5.0, 1.2, 0.8]), theta=2, seed=3, resample=1, init=1)

@@ -159,14 +159,27 @@ struct TiledArgs {
     uint64_t *H_out;          // [R] digest term of each replica, or nullptr
     int32_t *E_out;           // [R]
     uint32_t *Mt_out;         // [R] or nullptr
+    uint32_t dword;           // 1: the dword form also where the quad form applies
+    // quad form: rows of src / dst as colour-0 sites, then colour-1 sites; count
+    // the bonds after the launch's last half-sweep (of colour 1, with the one
+    // before in the same launch)
+    uint32_t src_planar, dst_planar, fuse;
+    uint32_t rs;              // rows of lanes of a workgroup of the runtime-side form
 };
 bool tiled_path(uint32_t L);
 uint32_t tiled_rows(uint32_t L);
 uint32_t tiled_max_halves(uint32_t L);   // half-sweeps fused per tiled launch
 hipError_t launch_tiled_half(const TiledArgs &a, hipStream_t s);
+// The quad form (pa_quad_tiled.h): whether it takes these sweeps, whether rows
+// may stay split by colour between its launches, a launch (one whole sweep).
+bool tiled_quads(const TiledArgs &a);
+bool tiled_planar(uint32_t L);
+hipError_t launch_tiled_quad(const TiledArgs &a, hipStream_t s);
 hipError_t launch_tiled_init(const TiledArgs &a, hipStream_t s);
 // energies (eq. (3)) and M~ (eq. (5)) of dst; leaves bonds and cnt zeroed
 hipError_t launch_tiled_measure(const TiledArgs &a, hipStream_t s);
+// the same where the sums are complete (counted by the last sweep launch)
+hipError_t launch_tiled_finalize(const TiledArgs &a, hipStream_t s);
 
 hipError_t launch_sweep(const SweepArgs &a, hipStream_t s);
 hipError_t launch_post(const PostArgs &a, hipStream_t s);

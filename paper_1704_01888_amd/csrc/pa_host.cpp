@@ -585,6 +585,7 @@ pa::TiledArgs tiled_args(pa_run_state *r, uint32_t i, const uint8_t *src, const 
     a.H_out = p.digest ? r->at<uint64_t>(p.off_H) : nullptr;
     a.E_out = r->at<int32_t>(p.off_E);
     a.Mt_out = p.mag ? r->at<uint32_t>(p.off_Mt) : nullptr;
+    a.dword = r->dword ? 1u : 0u;
     return a;
 }
 
@@ -592,22 +593,30 @@ pa::TiledArgs tiled_args(pa_run_state *r, uint32_t i, const uint8_t *src, const 
 // (theta = 0 copies).  A launch that fuses several half-sweeps recomputes the
 // rows next to its tile, so it must not read rows that neighbouring tiles of
 // the same launch write: no launch works in place.  The launches alternate
-// between dst and the spare buffer `x`, the last one writing dst.
+// between dst and the spare buffer `x`, the last one writing dst.  The quad form
+// keeps rows split by colour between its launches and counts the bonds in the
+// last one, unless states or digests are asked for.
 hipError_t launch_tiled_sweeps(pa::TiledArgs a, uint32_t theta, uint8_t *x, hipStream_t s) {
     hipError_t e;
     const uint32_t total = 2 * theta, S = pa::tiled_max_halves(a.L);
     const uint32_t launches = total == 0 ? 1u : (total + S - 1) / S;
     uint8_t *const dst = a.dst;
+    const bool quads = total != 0 && pa::tiled_quads(a), planar = quads && pa::tiled_planar(a.L);
+    const bool fuse = quads && !a.cnt && !a.Hacc;
     a.h0 = 0;
     for (uint32_t i = 0; i < launches; ++i) {
+        const bool last = i + 1 == launches;
         a.halves = std::min(total - a.h0, S);
         a.dst = ((launches - 1 - i) & 1u) ? x : dst;
-        if ((e = pa::launch_tiled_half(a, s)) != hipSuccess) return e;
+        a.src_planar = planar && i != 0;
+        a.dst_planar = planar && !last;
+        a.fuse = fuse && last;
+        if ((e = quads ? pa::launch_tiled_quad(a, s) : pa::launch_tiled_half(a, s)) != hipSuccess) return e;
         a.src = a.dst;
         a.anc = nullptr;
         a.h0 += a.halves;
     }
-    return pa::launch_tiled_measure(a, s);
+    return fuse ? pa::launch_tiled_finalize(a, s) : pa::launch_tiled_measure(a, s);
 }
 
 // Copy-count buffer of step parity `par`.

@@ -24,6 +24,7 @@
 // spread over several waves uses barriers.
 #include "pa_device.h"
 #include "pa_quad.h"
+#include "pa_quad_tiled.h"
 
 namespace pa {
 
@@ -1448,15 +1449,6 @@ __global__ void __launch_bounds__(256) k_prep_batch(const PrepRec *recs, const u
 // 2, fused).  Pair p = y*L/4 + x/4 uses the same Philox counters as in LDS,
 // so the result is the same as for a replica held in LDS.
 // ---------------------------------------------------------------------------
-// Workgroup -> (replica, tile): each XCD takes a contiguous range, so that
-// neighbouring tiles of a replica share their halo rows in one L2.
-__device__ __forceinline__ void tile_of(uint32_t tiles, uint32_t &k, uint32_t &tile) {
-    uint32_t b = blockIdx.x;
-    if ((gridDim.x & 7u) == 0) b = (b & 7u) * (gridDim.x >> 3) + (b >> 3);
-    k = b / tiles;
-    tile = b % tiles;
-}
-
 // Copies rows y0-1 .. y0+n (periodic) of replica src (L/4 dwords per row) to
 // LDS rows 0 .. n+1; with halo = false only rows y0 .. y0+n (LDS rows 1 .. n+1).
 __device__ __forceinline__ void load_tile_rows(uint32_t *lds32, const uint32_t *src32, uint32_t L,
@@ -2413,6 +2405,49 @@ static void *tiled_fixed_kernel(uint32_t L) {
     }
 }
 
+// The quad form takes q <= 32 with 32-bit thresholds; a population loaded with
+// other spins keeps the dword form (a.dword).
+bool tiled_quads(const TiledArgs &a) {
+    return a.q <= 32 && a.T[3] != 0 && !a.dword && tiled_max_halves(a.L) == QT_HALVES;
+}
+bool tiled_planar(uint32_t L) { return (L & 7u) == 0; }
+
+template <uint32_t UNIT>
+static void *tiled_quad_kernel(uint32_t L) {
+    switch (L) {
+        case 512: return (void *)k_tiled_quad<512, 256, UNIT>;
+        case 1024: return (void *)k_tiled_quad<1024, 256, UNIT>;
+        case 2048: return (void *)k_tiled_quad<2048, 256, UNIT>;
+        case 4096: return (void *)k_tiled_quad<4096, 512, UNIT>;
+        default: return nullptr;
+    }
+}
+
+hipError_t launch_tiled_quad(const TiledArgs &args, hipStream_t s) {
+    TiledArgs a = args;
+    const uint64_t blocks = (uint64_t)a.R * a.tiles;
+    if (blocks == 0) return hipSuccess;
+    void *f = a.rows == 16384u / a.L ? (a.q <= 16 ? tiled_quad_kernel<16>(a.L) : tiled_quad_kernel<32>(a.L)) : nullptr;
+    uint32_t threads = tiled_threads(a.L);
+    const uint32_t dpq = (a.L + 4u) / 8u;
+    if (!f) {
+        // four or eight waves (an uneven number per SIMD costs more than lanes
+        // left over), whichever spends fewer lane rounds on a tile's two
+        // half-sweeps
+        uint64_t best = ~0ull;
+        for (uint32_t t = 256; t <= 512; t += 256) {
+            const uint32_t rs = t / dpq;
+            if (rs == 0) continue;
+            const uint64_t cost = (uint64_t)t * ((a.rows + 2 + rs - 1) / rs + (a.rows + rs - 1) / rs);
+            if (cost < best) { best = cost; threads = t; a.rs = rs; }
+        }
+        f = a.q <= 16 ? (void *)k_tiled_quad<0, 0, 16> : (void *)k_tiled_quad<0, 0, 32>;
+    }
+    const size_t lds = (((size_t)(a.rows + 2 * QT_HALVES) * 8u * dpq + 15u) & ~size_t(15)) + quad_tab_bytes(a.q);
+    hipLaunchKernelGGL((void (*)(TiledArgs))f, dim3((uint32_t)blocks), dim3(threads), lds, s, a);
+    return hipGetLastError();
+}
+
 hipError_t launch_tiled_half(const TiledArgs &a, hipStream_t s) {
     const uint64_t blocks = (uint64_t)a.R * a.tiles;
     if (blocks == 0) return hipSuccess;
@@ -2441,7 +2476,11 @@ hipError_t launch_tiled_measure(const TiledArgs &a, hipStream_t s) {
     if (blocks == 0) return hipSuccess;
     const size_t lds = (size_t)(a.rows + 2) * a.L + 4 * 256;
     hipLaunchKernelGGL(k_tiled_measure, dim3((uint32_t)blocks), dim3(256), lds, s, a);
-    hipLaunchKernelGGL(k_tiled_finalize, dim3((a.R + 255) / 256), dim3(256), 0, s, a);
+    return launch_tiled_finalize(a, s);
+}
+
+hipError_t launch_tiled_finalize(const TiledArgs &a, hipStream_t s) {
+    if (a.R) hipLaunchKernelGGL(k_tiled_finalize, dim3((a.R + 255) / 256), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

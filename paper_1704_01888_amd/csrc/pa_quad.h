@@ -47,7 +47,7 @@ namespace {
 //     waves 1156 attempts/ns, 24 lanes in 12 waves 1424; 96x96 with 384 lanes
 //     in 6 waves 1156, in 12 waves 1419).
 //   - nr_waves: NR > 1 is used from launches of that many waves (counted with
-//     one replica per lane) on, four rounds of the GPU's 8192 wave slots, or
+//     one replica per lane) on, eight rounds of the GPU's 8192 wave slots, or
 //     twelve where 12-wave workgroups make the last round coarser (NR = 1 /
 //     largest, attempts per ns at theta = 10: 32x32 1142 / 1085 with 16000
 //     waves, 1250 / 1242 with 32000, 1336 / 1343 with 64000, and the same for
@@ -55,12 +55,12 @@ namespace {
 //     64000).
 struct QuadShape { uint32_t max_nr, nr_waves, wpe_max, wpe_one; bool hoist; };
 constexpr QuadShape quad_shape(uint32_t L, uint32_t G) {
-    if (L == 8 && G == 8) return {4, 32768, 7, 8, true};
-    if (L == 16 && G == 32) return {4, 32768, 6, 8, true};
+    if (L == 8 && G == 8) return {4, 65536, 7, 8, true};
+    if (L == 16 && G == 32) return {4, 65536, 6, 8, true};
     if (L == 24 && G == 24) return {2, 98304, 6, 8, true};
-    if (L == 32 && G == 128) return {4, 32768, 8, 8, true};
+    if (L == 32 && G == 128) return {4, 65536, 8, 8, true};
     if (L == 48 && G == 96) return {2, 98304, 6, 6, true};
-    if (L == 64 && G == 512) return {4, 32768, 8, 8, true};
+    if (L == 64 && G == 512) return {4, 65536, 8, 8, true};
     if (L == 96 && G == 384) return {2, 98304, 6, 6, true};
     if (L == 128 && G == 1024) return {2, 24576, 8, 8, true};
     if (L == 128 && G == 512) return {1, 0, 8, 8, true};
@@ -155,13 +155,8 @@ __device__ __forceinline__ QuadPrefix quad_prefix(uint32_t P0_hi, uint32_t c3k1,
     return QuadPrefix{(uint32_t)q1, (uint64_t)PHILOX_M0 * c0};
 }
 
-// Rounds 3 (rest) to 10.  r1: the other product of round 3, which depends on
-// the pair and the replica only (r1k: its high word xor the round key); c3k:
-// word 3 after round 2 xor the second key of round 3.
-__device__ __forceinline__ uint4 quad_rounds(const QuadPrefix &f, uint32_t r1_lo, uint32_t r1k, uint32_t c3k,
-                                             const SweepKey &s) {
-    uint32_t c0 = r1k ^ f.q1_lo, c1 = r1_lo;
-    uint32_t c2 = (uint32_t)(f.r0 >> 32) ^ c3k, c3 = (uint32_t)f.r0;
+// Rounds 4 to 10 after round 3's words.
+__device__ __forceinline__ uint4 quad_rounds(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, const SweepKey &s) {
 #pragma unroll
     for (int r = 3; r < 10; ++r) {
         const uint64_t x0 = (uint64_t)PHILOX_M0 * c0;
@@ -174,6 +169,18 @@ __device__ __forceinline__ uint4 quad_rounds(const QuadPrefix &f, uint32_t r1_lo
         c2 = m2;
     }
     return make_uint4(c0, c1, c2, c3);
+}
+
+// Rounds 3 (rest) to 10.  r1: the other product of round 3, which depends on
+// the pair and the replica only, whole or as its low word and its high word
+// xor the round key; c3k: word 3 after round 2 xor the second key of round 3.
+__device__ __forceinline__ uint4 quad_block(const QuadPrefix &f, uint32_t r1_lo, uint32_t r1k, uint32_t c3k,
+                                            const SweepKey &s) {
+    return quad_rounds(r1k ^ f.q1_lo, r1_lo, (uint32_t)(f.r0 >> 32) ^ c3k, (uint32_t)f.r0, s);
+}
+__device__ __forceinline__ uint4 quad_block(const QuadPrefix &f, uint64_t r1, uint32_t c3k, const SweepKey &s) {
+    return quad_rounds(xor3((uint32_t)(r1 >> 32), f.q1_lo, s.k0[2]), (uint32_t)r1, (uint32_t)(f.r0 >> 32) ^ c3k,
+                       (uint32_t)f.r0, s);
 }
 
 // Flags (UNIT per byte) of the unequal / equal bytes of a and b, all below UNIT.
@@ -331,20 +338,16 @@ __device__ __forceinline__ void sweeps_quad(uint32_t *lds32, uint32_t g, bool on
                         U = perm(up[(int32_t)vs], U, sel_v);
                         Dn = perm(dn[(int32_t)vs], Dn, sel_v);
                     }
-                    uint32_t la, ka, lb1, kb;
+                    uint4 wa, wb;
                     if constexpr (HOIST) {
-                        la = r1_lo[j][r][0]; ka = r1k[j][r][0];
-                        lb1 = r1_lo[j][r][1]; kb = r1k[j][r][1];
+                        wa = quad_block(f0, r1_lo[j][r][0], r1k[j][r][0], c3k[r], key);
+                        wb = quad_block(f1, r1_lo[j][r][1], r1k[j][r][1], c3k[r], key);
                     } else {
                         uint32_t lo = lo0 + PHILOX_M0 * (j * (RS * H / 2u));
                         asm("" : "+v"(lo));        // recomputed per half-sweep, not kept
-                        const uint64_t ra = (uint64_t)PHILOX_M1 * (lo ^ u2[r]);
-                        const uint64_t rb = (uint64_t)PHILOX_M1 * ((lo + PHILOX_M0) ^ u2[r]);
-                        la = (uint32_t)ra; ka = (uint32_t)(ra >> 32) ^ key.k0[2];
-                        lb1 = (uint32_t)rb; kb = (uint32_t)(rb >> 32) ^ key.k0[2];
+                        wa = quad_block(f0, (uint64_t)PHILOX_M1 * (lo ^ u2[r]), c3k[r], key);
+                        wb = quad_block(f1, (uint64_t)PHILOX_M1 * ((lo + PHILOX_M0) ^ u2[r]), c3k[r], key);
                     }
-                    const uint4 wa = quad_rounds(f0, la, ka, c3k[r], key);
-                    const uint4 wb = quad_rounds(f1, lb1, kb, c3k[r], key);
                     own[g] = update_quad<UNIT>(D, perm(Ax, A, sel), A, U, Dn, wa, wb, qm1, base);
                 }
             }

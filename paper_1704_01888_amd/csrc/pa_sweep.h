@@ -199,6 +199,15 @@ __device__ __forceinline__ unsigned long long wave_sum_all(unsigned long long v)
     return v;
 }
 
+// Workgroup -> (replica, tile): each XCD takes a contiguous range, so that
+// neighbouring tiles of a replica share their halo rows in one L2.
+__device__ __forceinline__ void tile_of(uint32_t tiles, uint32_t &k, uint32_t &tile) {
+    uint32_t b = blockIdx.x;
+    if ((gridDim.x & 7u) == 0) b = (b & 7u) * (gridDim.x >> 3) + (b >> 3);
+    k = b / tiles;
+    tile = b % tiles;
+}
+
 // Index of the segment holding `block`: the last r < n with start[r] <= block
 // (start is non-decreasing from start[0] = 0, so segments without workgroups
 // are skipped).  Each wave counts the starts not after `block`, 64 per round

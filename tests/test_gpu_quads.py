@@ -117,3 +117,32 @@ def test_sides_without_lane_choices_match_the_oracle(ctx, L):
 def test_side_without_lane_choices_from_ground_states_to_64_bit_thresholds(ctx):
     for L in (18, 36, 50):
         _check(ctx, L=L, q=6, R=40, beta=np.array([6.0, 5.0, 1.2, 0.8]), theta=2, seed=3, resample=1, init=1)
+
+
+@pytest.mark.parametrize("L,R,theta", [(260, 5, 2), (264, 4, 3), (300, 3, 1), (308, 3, 2), (512, 3, 2), (1024, 2, 3),
+                                       (1028, 2, 1), (2048, 2, 1), (4092, 1, 1), (4096, 1, 1)], ids=lambda v: str(v))
+def test_tiled_quads_match_the_oracle(ctx, L, R, theta):
+    """Rows of whole and half dwords per colour, ragged last tiles, one to three
+    launches per step; with the bonds counted by the last launch (energies and
+    spins only) and by the measuring pass (states and digests too)."""
+    for q, outputs in ((16, pa.OUT_FINAL | pa.OUT_HIST), (17, ALL), (32, pa.OUT_FINAL | pa.OUT_HIST)):
+        print(f"\nL={L} q={q} R={R} theta={theta}", flush=True)
+        kw = dict(L=L, q=q, R=R, beta=linear_betas(1.6, 2 if L < 2000 else 1), theta=theta, seed=L + q, resample=1)
+        got = pa.pa_run(ctx, pa.Desc(outputs=outputs, **kw))
+        want = oracle.run(oracle.Desc(**kw), final=True, hist=True, magnetisation=True, digest=True)
+        for key in KEYS:
+            if key in got:
+                assert (got[key] == want[key]).all(), key
+
+
+def test_tiled_population_loaded_with_spins_beyond_q(ctx):
+    kw = dict(L=264, q=3, R=3, beta=linear_betas(1.0, 4), theta=2, seed=9, resample=2)
+    spins = np.random.default_rng(2).integers(0, 100, size=(3, 264 * 264), dtype=np.uint8)
+    run = pa.Run(ctx, pa.Desc(**kw))
+    run.load(1, spins, 0.0)
+    run.advance(1)
+    got = run.read()
+    run.finish()
+    od = oracle.Desc(**kw)
+    for j in range(3):
+        assert (got["spins"][j] == oracle.sweep_replica(od, 2, j, spins[j])).all()

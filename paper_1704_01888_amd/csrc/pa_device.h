@@ -29,8 +29,9 @@ struct SweepArgs {
     uint32_t key0, key1;      // Philox key
     uint32_t G;               // lanes per replica: a power of two up to 64 (several replicas
                               // per wave) or a multiple of 64 (one replica per workgroup)
-    uint32_t waves_per_block;
-    uint32_t dword;           // 1: the dword kernel also where the quad kernel has the shape
+    uint16_t waves_per_block;
+    uint16_t dword;           // 1: the dword kernel also where the quad kernel has the shape
+    uint32_t big;             // quad kernel: the first workgroups, with several replicas per lane
 };
 
 // The resampling into step `step` of a population small enough for one
@@ -282,6 +283,8 @@ bool quad_only(uint32_t L, uint32_t G, uint32_t waves_per_block);
 size_t shape_lds_bytes(uint32_t L, uint32_t q, uint32_t G, uint32_t waves_per_block, uint32_t q_counters);
 struct SweepLaunch { uint32_t cls, blocks; uint64_t per_block; size_t lds; };
 uint32_t settle_sweep(SweepArgs &a, uint64_t replicas);
+// Of the `replicas` of a quad launch, those to be held one per lane (the last).
+uint64_t quad_singles(const SweepArgs &a, uint32_t nr, uint64_t replicas);
 SweepLaunch sweep_launch(const SweepArgs &a, uint32_t nr);
 // index of L in the table of lattices with lane choices (-1: none), and its size
 int lane_choice_index(uint32_t L);

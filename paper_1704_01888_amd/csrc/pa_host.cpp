@@ -555,7 +555,7 @@ pa::SweepArgs sweep_args(pa_run_state *r, uint32_t i, uint32_t mode, const uint8
     a.key0 = (uint32_t)(p.desc.seed & 0xffffffffu);
     a.key1 = (uint32_t)(p.desc.seed >> 32);
     a.G = r->G;
-    a.waves_per_block = r->wpb;
+    a.waves_per_block = (uint16_t)r->wpb;
     a.dword = r->dword ? 1u : 0u;
     return a;
 }
@@ -1875,10 +1875,28 @@ StepLaunch build_step(const std::vector<pa_run_state *> &active, std::vector<uin
     };
     std::map<uint64_t, uint64_t> replicas;
     for (const SW &e : sw) replicas[shape_key(e.a)] += e.a.R_new;
-    for (SW &e : sw) {
-        const uint32_t nr = pa::settle_sweep(e.a, replicas[shape_key(e.a)]);
-        e.l = pa::sweep_launch(e.a, nr);
-        e.threads = 64u * e.a.waves_per_block;
+    std::vector<uint32_t> nr;
+    for (SW &e : sw) nr.push_back(pa::settle_sweep(e.a, replicas[shape_key(e.a)]));
+    // several replicas per lane in the first runs of a launch, one in the last
+    replicas.clear();
+    for (size_t k = 0; k < sw.size(); ++k)
+        if (nr[k] > 1) replicas[shape_key(sw[k].a)] += sw[k].a.R_new;
+    std::map<uint64_t, uint64_t> singles;
+    for (size_t k = sw.size(); k-- > 0;) {
+        pa::SweepArgs &a = sw[k].a;
+        if (nr[k] > 1) {
+            const uint64_t key = shape_key(a), want = pa::quad_singles(a, nr[k], replicas[key]);
+            if (replicas[key] <= want) {
+                nr[k] = 1;
+            } else {
+                uint64_t &done = singles[key];
+                const uint64_t one = std::min<uint64_t>(a.R_new, want - std::min(want, done));
+                done += one;
+                a.big = (uint32_t)((a.R_new - one) / pa::sweep_launch(a, nr[k]).per_block);
+            }
+        }
+        sw[k].l = pa::sweep_launch(a, nr[k]);
+        sw[k].threads = 64u * a.waves_per_block;
     }
     // sweep groups: runs of one kernel class contiguous in the table
     // (a class's runs may differ in waves per workgroup when tuned shapes

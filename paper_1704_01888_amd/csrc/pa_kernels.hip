@@ -26,6 +26,8 @@
 #include "pa_quad.h"
 #include "pa_quad_tiled.h"
 
+#include <algorithm>
+
 namespace pa {
 
 namespace {
@@ -2156,7 +2158,8 @@ uint32_t sweep_max_nr(const SweepArgs &a) {
 }
 
 // Settles the kernel of a sweep in a launch that holds `replicas` of its class
-// in all and returns its replicas per lane (0: not the quad kernel).
+// in all and returns its largest number of replicas per lane (0: not the quad
+// kernel).
 //   - A step the quad kernel does not take, with a shape only it has: the
 //     dword kernel's default shape.
 //   - Sides with lane choices: such a shape needs a launch of QUAD_MIN_WAVES,
@@ -2166,27 +2169,39 @@ uint32_t sweep_max_nr(const SweepArgs &a) {
 //     767 / 865 and 1062 / 984; 96x96 767 / 891 and 1070 / 973).
 //   - Other sides: workgroups of fewer waves until there are two per compute
 //     unit.
-//   - Several replicas per lane leave fewer and longer waves, which pays from
-//     the shape's nr_waves on (see quad_shape).
 constexpr uint64_t QUAD_MIN_WAVES = 6144, QUAD_MIN_BLOCKS = 512;
+static void default_shape(SweepArgs &a, void (*shape)(uint32_t, uint32_t, uint32_t *, uint32_t *)) {
+    uint32_t w;
+    shape(a.L, 0, &a.G, &w);
+    a.waves_per_block = (uint16_t)w;
+}
 uint32_t settle_sweep(SweepArgs &a, uint64_t replicas) {
     uint32_t max_nr = sweep_max_nr(a);
     if (max_nr == 0) {
-        if (quad_only(a.L, a.G, a.waves_per_block)) dword_shape(a.L, 0, &a.G, &a.waves_per_block);
+        if (quad_only(a.L, a.G, a.waves_per_block)) default_shape(a, dword_shape);
         return 0;
     }
     if (quad_any_side(a.L)) {
         const uint32_t least = (a.G + 63u) / 64u;
         while (a.waves_per_block > least && replicas < QUAD_MIN_BLOCKS * (64u * a.waves_per_block / a.G))
-            a.waves_per_block = a.waves_per_block >= least + 4u ? a.waves_per_block - 4u : least;
+            a.waves_per_block = (uint16_t)(a.waves_per_block >= least + 4u ? a.waves_per_block - 4u : least);
         return max_nr;
     }
     if (quad_only(a.L, a.G, a.waves_per_block) && replicas * a.G / 64u < QUAD_MIN_WAVES) {
-        sweep_shape(a.L, 0, &a.G, &a.waves_per_block);
+        default_shape(a, sweep_shape);
         max_nr = sweep_max_nr(a);
     }
-    if (max_nr <= 1) return max_nr;
-    return replicas * a.G / 64u >= quad_shape(a.L, a.G).nr_waves ? max_nr : 1u;
+    return max_nr;
+}
+
+// (see quad_shape; all of them below two shares, where the long waves would be
+// too few: 32x32, R = 10000 with magnetisation 8415 us a run against 8270)
+uint64_t quad_singles(const SweepArgs &a, uint32_t nr, uint64_t replicas) {
+    constexpr uint64_t CUS = 256;
+    const uint32_t w = a.waves_per_block;
+    const uint64_t slots = CUS * (4u * quad_shape(a.L, a.G).wpe_max / w * w);
+    const uint64_t share = slots * 64u / a.G * (nr > 2 ? 3u : 4u) / 2u;
+    return replicas < 2u * share ? replicas : share;
 }
 
 // Launch shape of a sweep: its class, replicas per workgroup and LDS.  nr: the
@@ -2199,13 +2214,24 @@ SweepLaunch sweep_launch(const SweepArgs &a, uint32_t nr) {
                      : replicas_per_block(a.G, a.waves_per_block);
     l.lds = nr ? quad_lds_bytes(a.L, a.G, a.waves_per_block, nr, a.q, qc)
                : sweep_lds_bytes(a.N, a.G, a.waves_per_block, qc);
-    l.blocks = (uint32_t)((a.R_new + l.per_block - 1) / l.per_block);
+    if (nr > 1) {                      // a.big workgroups of nr replicas per lane, then single ones
+        const uint64_t one = l.per_block / nr, done = std::min<uint64_t>(a.R_new, a.big * l.per_block);
+        l.blocks = a.big + (uint32_t)((a.R_new - done + one - 1) / one);
+    } else {
+        l.blocks = (uint32_t)((a.R_new + l.per_block - 1) / l.per_block);
+    }
     return l;
 }
 
 hipError_t launch_sweep(const SweepArgs &args, hipStream_t s) {
     SweepArgs a = args;
-    const uint32_t nr = settle_sweep(a, a.R_new);
+    uint32_t nr = settle_sweep(a, a.R_new);
+    if (nr > 1) {
+        const uint64_t singles = quad_singles(a, nr, a.R_new);
+        if (a.R_new > singles)
+            a.big = (uint32_t)((a.R_new - singles) / quad_replicas_per_block(a.G, a.waves_per_block, nr));
+        if (a.big == 0) nr = 1;
+    }
     const SweepLaunch l = sweep_launch(a, nr);
     if (l.blocks == 0) return hipSuccess;
     void *kern = sweep_kernel(l.cls, false);

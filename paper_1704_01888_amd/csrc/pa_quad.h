@@ -46,27 +46,29 @@ namespace {
 //     the four SIMDs unevenly between barriers (24x24 with 72 lanes in 9
 //     waves 1156 attempts/ns, 24 lanes in 12 waves 1424; 96x96 with 384 lanes
 //     in 6 waves 1156, in 12 waves 1419).
-//   - nr_waves: NR > 1 is used from launches of that many waves (counted with
-//     one replica per lane) on, eight rounds of the GPU's 8192 wave slots, or
-//     twelve where 12-wave workgroups make the last round coarser (NR = 1 /
-//     largest, attempts per ns at theta = 10: 32x32 1142 / 1085 with 16000
-//     waves, 1250 / 1242 with 32000, 1336 / 1343 with 64000, and the same for
-//     8x8, 16x16 and 64x64; 96x96 1257 / 1194 with 32000, 1325 / 1320 with
-//     64000).
-struct QuadShape { uint32_t max_nr, nr_waves, wpe_max, wpe_one; bool hoist; };
+//   - A launch holds its first replicas NR per lane and the last `rounds`
+//     rounds of the GPU's wave slots one per lane: the short waves at the end
+//     leave fewer slots empty than a last partial round of long ones.  Rate at
+//     theta = 10, all one per lane / all NR / mixed so, attempts per ns: 32x32
+//     R = 20000 1283 / 1287 / 1315, 50000 1359 / 1406 / 1440; 64x64 4000 1266 /
+//     1267 / 1290, 16000 1377 / 1422 / 1450; 16x16 100000 1318 / 1290 / 1380;
+//     96x96 5000 1298 / 1333 / 1331, 5333 1257 / 1194; 128x128 2000 1328 / 1358
+//     / 1347.  Two rounds, not one and a half, for NR = 2 (96x96 R = 2000: 1186
+//     with 36 % of the replicas in pairs, 1250 with none).
+struct QuadShape { uint32_t max_nr, wpe_max, wpe_one; bool hoist; };
 constexpr QuadShape quad_shape(uint32_t L, uint32_t G) {
-    if (L == 8 && G == 8) return {4, 65536, 7, 8, true};
-    if (L == 16 && G == 32) return {4, 65536, 6, 8, true};
-    if (L == 24 && G == 24) return {2, 98304, 6, 8, true};
-    if (L == 32 && G == 128) return {4, 65536, 8, 8, true};
-    if (L == 48 && G == 96) return {2, 98304, 6, 6, true};
-    if (L == 64 && G == 512) return {4, 65536, 8, 8, true};
-    if (L == 96 && G == 384) return {2, 98304, 6, 6, true};
-    if (L == 128 && G == 1024) return {2, 24576, 8, 8, true};
-    if (L == 128 && G == 512) return {1, 0, 8, 8, true};
-    if (L == 192 && G == 768) return {1, 0, 6, 6, true};
-    if (L == 256 && G == 1024) return {1, 0, 8, 8, false};
-    return {0, 0, 0, 0, false};
+    if (L == 8 && G == 8) return {4, 7, 8, true};
+    if (L == 16 && G == 32) return {4, 6, 8, true};
+    if (L == 24 && G == 24) return {2, 6, 8, true};
+    if (L == 32 && G == 128) return {4, 8, 8, true};
+    if (L == 48 && G == 96) return {2, 6, 6, true};
+    if (L == 64 && G == 512) return {4, 8, 8, true};
+    if (L == 96 && G == 384) return {2, 6, 6, true};
+    if (L == 128 && G == 1024) return {2, 8, 8, true};
+    if (L == 128 && G == 512) return {1, 8, 8, true};
+    if (L == 192 && G == 768) return {1, 6, 6, true};
+    if (L == 256 && G == 1024) return {1, 8, 8, false};
+    return {0, 0, 0, false};
 }
 
 // How the rows of a side lie in a plane.  A row has H = L/2 sites of a colour in
@@ -367,9 +369,10 @@ __device__ __forceinline__ uint8_t *quad_site(uint8_t *rep, uint32_t y, uint32_t
 // One workgroup `block` of a quad sweep launch: gather or create its replicas,
 // theta sweeps, energies (and M~), store, as sweep_body does.  The workgroup
 // holds blockDim / G groups of G lanes, each NR replicas with consecutive
-// slots.  ANY: a side without a table entry (lanes may be left over).
+// slots, from slot `first` on.  ANY: a side without a table entry (lanes may be
+// left over).
 template <uint32_t LT, uint32_t GT, uint32_t NR, uint32_t UNIT, bool HOIST, bool ANY>
-__device__ __forceinline__ void sweep_quad_body(const SweepArgs &a, uint32_t block) {
+__device__ __forceinline__ void sweep_quad_body(const SweepArgs &a, uint32_t block, uint32_t first) {
     extern __shared__ __align__(16) uint8_t smem[];
     using Geo = QuadGeo<LT, GT>;
     constexpr uint32_t L = LT, N = L * L, G = GT, DPQ = Geo::DPQ, PLANE = Geo::PLANE;
@@ -397,7 +400,7 @@ __device__ __forceinline__ void sweep_quad_body(const SweepArgs &a, uint32_t blo
     }
 
     uint32_t k[NR];
-    const uint64_t k0 = ((uint64_t)block * groups + gi) * NR;
+    const uint64_t k0 = first + ((uint64_t)block * groups + gi) * NR;
 #pragma unroll
     for (uint32_t r = 0; r < NR; ++r)
         k[r] = G % 64u == 0 ? __builtin_amdgcn_readfirstlane((uint32_t)k0 + r) : (uint32_t)k0 + r;
@@ -496,7 +499,7 @@ __device__ __forceinline__ void sweep_quad_body(const SweepArgs &a, uint32_t blo
         }
     }
     __syncthreads();
-    if (WAVE && (uint64_t)block * rpb + (uint64_t)((tid & ~63u) / G) * NR >= a.R_new) return;   // an idle wave
+    if (WAVE && first + (uint64_t)block * rpb + (uint64_t)((tid & ~63u) / G) * NR >= a.R_new) return;   // an idle wave
 
     const uint32_t base = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t *)smem + tab +
                           8u * (tid % (UNIT / 8u));
@@ -655,10 +658,22 @@ constexpr uint32_t quad_wpe(uint32_t L, uint32_t G, uint32_t NR) {
     return NR == 1 ? quad_shape(L, G).wpe_one : quad_shape(L, G).wpe_max;
 }
 
+// The first a.big workgroups hold NR replicas per lane, the rest one: long waves
+// first, short ones fill the end of the launch.
+template <uint32_t LT, uint32_t GT, uint32_t NR, uint32_t UNIT>
+__device__ __forceinline__ void sweep_quad_mixed(const SweepArgs &a, uint32_t block) {
+    constexpr bool HOIST = quad_shape(LT, GT).hoist;
+    if (NR == 1 || block < a.big) {
+        sweep_quad_body<LT, GT, NR, UNIT, HOIST, false>(a, block, 0);
+    } else {
+        sweep_quad_body<LT, GT, 1, UNIT, HOIST, false>(a, block - a.big, a.big * (blockDim.x / GT) * NR);
+    }
+}
+
 template <uint32_t LT, uint32_t GT, uint32_t NR, uint32_t UNIT>
 __global__ void __attribute__((amdgpu_flat_work_group_size(64, 1024), amdgpu_waves_per_eu(quad_wpe(LT, GT, NR))))
 k_sweep_quad(SweepArgs a) {
-    sweep_quad_body<LT, GT, NR, UNIT, quad_shape(LT, GT).hoist, false>(a, blockIdx.x);
+    sweep_quad_mixed<LT, GT, NR, UNIT>(a, blockIdx.x);
 }
 
 // Batched form: run r owns workgroups start[r] .. start[r+1]-1.
@@ -667,14 +682,14 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(64, 1024), amdgpu_wav
 k_sweep_quad_batch(const SweepArgs *runs, const uint32_t *start, uint32_t n) {
     const uint32_t r = segment_of(start, n, blockIdx.x);
     const SweepArgs &a = runs[r];    // by reference: a copy would go to scratch memory
-    sweep_quad_body<LT, GT, NR, UNIT, quad_shape(LT, GT).hoist, false>(a, blockIdx.x - start[r]);
+    sweep_quad_mixed<LT, GT, NR, UNIT>(a, blockIdx.x - start[r]);
 }
 
 // The sides without a table entry (shape quad_any, 32 states).
 template <uint32_t LT>
 __global__ void __attribute__((amdgpu_flat_work_group_size(64, 64 * quad_any(LT).waves), amdgpu_waves_per_eu(quad_any(LT).wpe)))
 k_sweep_any(SweepArgs a) {
-    sweep_quad_body<LT, quad_any(LT).G, 1, 32, quad_any(LT).hoist, true>(a, blockIdx.x);
+    sweep_quad_body<LT, quad_any(LT).G, 1, 32, quad_any(LT).hoist, true>(a, blockIdx.x, 0);
 }
 
 template <uint32_t LT>
@@ -682,7 +697,7 @@ __global__ void __attribute__((amdgpu_flat_work_group_size(64, 64 * quad_any(LT)
 k_sweep_any_batch(const SweepArgs *runs, const uint32_t *start, uint32_t n) {
     const uint32_t r = segment_of(start, n, blockIdx.x);
     const SweepArgs &a = runs[r];
-    sweep_quad_body<LT, quad_any(LT).G, 1, 32, quad_any(LT).hoist, true>(a, blockIdx.x - start[r]);
+    sweep_quad_body<LT, quad_any(LT).G, 1, 32, quad_any(LT).hoist, true>(a, blockIdx.x - start[r], 0);
 }
 
 }  // namespace

@@ -146,3 +146,21 @@ def test_tiled_population_loaded_with_spins_beyond_q(ctx):
     od = oracle.Desc(**kw)
     for j in range(3):
         assert (got["spins"][j] == oracle.sweep_replica(od, 2, j, spins[j])).all()
+
+
+@pytest.mark.parametrize("L,G,w,R", [(8, 8, 4, 131077), (16, 32, 4, 32771), (32, 128, 2, 9001), (64, 512, 8, 2601)],
+                         ids=lambda v: str(v))
+def test_launch_of_several_and_single_replicas_per_lane(ctx, L, G, w, R):
+    """Populations above the share of a launch that is held one replica per
+    lane, alone and as two runs of a batch (the second all single)."""
+    for r_class in range(4):
+        ctx.tune_set(L, 0, r_class, G, w)
+    kw = dict(L=L, q=7, beta=linear_betas(0.05, 2), theta=2, resample=1)
+    print(f"\nL={L} R={R}", flush=True)
+    _check(ctx, R=R, seed=L, **kw)
+    runs = [dict(R=R, seed=L + 1, **kw), dict(R=R // 2, seed=L + 2, **kw)]
+    got = pa.pa_run_batch(ctx, [pa.Desc(outputs=ALL, **r) for r in runs])
+    for r, g in zip(runs, got):
+        want = oracle.run(oracle.Desc(**r), final=True, hist=True, magnetisation=True, digest=True)
+        for key in KEYS:
+            assert (g[key] == want[key]).all(), (key, r["R"])

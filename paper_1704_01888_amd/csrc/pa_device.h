@@ -72,9 +72,9 @@ struct PostArgs {
     double *lnQ;              // [K]
     double *mbF;              // [K]   -beta F
     int32_t *E_ref;           // [K]   reference energy used by step i+1
-    // weights of the resampling to step i+1: workgroup 0 of a post launch
-    // computes the statistics above, workgroups 1, 2, ... the inclusive scan
-    // C over blocks of `wblock` replicas each
+    // weights of the resampling to step i+1: the first workgroups of a post
+    // launch compute the statistics (post_stats_blocks), the others the
+    // inclusive scan C over blocks of `wblock` replicas each
     uint32_t do_weights;
     uint32_t wblock;          // replicas per weight workgroup (scan_block(R_i))
     const int32_t *E;         // [R_i] energies of the population at step i
@@ -132,10 +132,12 @@ __host__ __device__ inline uint32_t scan_block(uint64_t n) {
     const uint64_t rows = (n + row * max_blocks - 1) / (row * max_blocks);
     return (uint32_t)(row * (rows ? rows : 1));
 }
-// Workgroups of a post launch: statistics, the weight blocks, and the
-// resampling workgroup of a small population.
+// Workgroups of a post launch: statistics (of the energies; of M~ and the
+// digest, where asked for), the weight blocks, and the resampling workgroup of
+// a small population.
+__host__ __device__ inline uint32_t post_stats_blocks(const PostArgs &a) { return a.Mt || a.H ? 2u : 1u; }
 __host__ __device__ inline uint32_t post_blocks(const PostArgs &a) {
-    return 1u + (a.do_weights ? (uint32_t)((a.R_i + a.wblock - 1) / a.wblock) : 0u) + (a.small ? 1u : 0u);
+    return post_stats_blocks(a) + (a.do_weights ? (uint32_t)((a.R_i + a.wblock - 1) / a.wblock) : 0u) + (a.small ? 1u : 0u);
 }
 __host__ __device__ inline uint32_t countfill_blocks(const SlotmapArgs &m) {
     return (uint32_t)((m.R_prev + m.block - 1) / m.block);

@@ -1014,17 +1014,23 @@ __device__ __forceinline__ void weight_block(const int32_t *E, uint32_t first, u
 // ---------------------------------------------------------------------------
 // k_post(i), workgroup 0: the exact integer sums behind the population
 // averages of eq. (4) and ln Q_{i+1} of Sec. 2 step 2 / eq. (2) from the energy
-// histogram of step i, the magnetisation sum, the integer part of the widths
-// and the digest (the averages and the widths themselves are formed on the
-// host; FP64 on the device is the ln Q / -beta F chain only).  Workgroups 1, 2, ...: if resampling follows, the integer
-// weights W(|E_j - E_ref|) of step i+1 and their inclusive scan C, one block
-// of replicas each.
+// histogram of step i, and the integer part of its width.  Where M~ or the
+// digest is asked for, one workgroup more: the M~ sum, histogram and width, and
+// the digest.  (The averages and the widths themselves are formed on the host;
+// FP64 on the device is the ln Q / -beta F chain only.)  The other workgroups:
+// if resampling follows, the integer weights W(|E_j - E_ref|) of step i+1 and
+// their inclusive scan C, one block of replicas each.
+//
+// A launch lasts as long as its slowest workgroup, a chain of memory and LDS
+// latencies.  With the M~ statistics after those of the energies in workgroup 0
+// that chain was the longest: 32x32, R = 1e4, with widths 21.7 -> 12.6 us; four
+// 64x64 runs of R = 1e3 27.8 -> 17.9 us.
 // ---------------------------------------------------------------------------
 // V: values per thread and load round of the population passes (the team
 // kernel's smaller populations take fewer, and fewer registers).
 template <uint32_t V = 32, bool LEAN = false>
-__device__ __forceinline__ void post_stats(const PostArgs &a, uint32_t *lds_hist, uint64_t *scratch,
-                                           uint32_t lds_cap = POST_LDS_BINS) {
+__device__ __forceinline__ void post_energy(const PostArgs &a, uint32_t *lds_hist, uint64_t *scratch,
+                                            uint32_t lds_cap = POST_LDS_BINS) {
     __shared__ double s_w[WG_WAVES];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const uint32_t nb = a.nbins;
@@ -1068,8 +1074,12 @@ __device__ __forceinline__ void post_stats(const PostArgs &a, uint32_t *lds_hist
     __syncthreads();
     if (a.store_hist) store_hist(he.v, a.hist);
     if (a.widths) hist_fwhm_ints<LEAN>(he.v, a.bin_e, scratch, a.fw_e + 8 * (size_t)a.step);
-    __syncthreads();
+}
 
+template <uint32_t V = 32, bool LEAN = false>
+__device__ __forceinline__ void post_magnet(const PostArgs &a, uint32_t *lds_hist, uint64_t *scratch,
+                                            uint32_t lds_cap = POST_LDS_BINS) {
+    const uint32_t tid = threadIdx.x;
     if (a.H) {
         // digest of the population: the sum of the replicas' terms
         uint64_t dsum = 0;
@@ -1084,9 +1094,7 @@ __device__ __forceinline__ void post_stats(const PostArgs &a, uint32_t *lds_hist
         if (tid == 0) a.Mt_sum[a.step] = hm.sum;
         if (a.store_hist) store_hist(hm.v, a.mhist);
         if (a.widths) hist_fwhm_ints<LEAN>(hm.v, a.bin_m, scratch, a.fw_m + 8 * (size_t)a.step);
-        __syncthreads();
     }
-
 }
 
 // A population of at most 32 blockDim 4-byte values held in registers, in
@@ -1235,8 +1243,11 @@ __device__ __forceinline__ void small_resample_body(const SmallResample &st, uin
 __device__ __forceinline__ void post_block(const PostArgs &a, uint32_t b) {
     __shared__ __align__(16) uint32_t lds[POST_LDS_BINS];
     __shared__ uint64_t scratch[17];
+    const uint32_t stats = post_stats_blocks(a);
     if (b == 0) {
-        post_stats(a, lds, scratch);
+        post_energy(a, lds, scratch);
+    } else if (b < stats) {
+        post_magnet(a, lds, scratch);
     } else if (a.small) {
         // the whole resampling into step i+1 (R_prev <= SMALL_RESAMPLE_MAX:
         // counts and cumulative weights take 12 bytes per replica of LDS)
@@ -1244,7 +1255,7 @@ __device__ __forceinline__ void post_block(const PostArgs &a, uint32_t b) {
         // (inlined: the record stays in the kernel arguments)
         small_resample_body(a.rs, nullptr, lds, C, scratch, true);
     } else {
-        post_weights(a, b - 1, lds, scratch);
+        post_weights(a, b - stats, lds, scratch);
     }
 }
 
@@ -1893,7 +1904,9 @@ __device__ __attribute__((noinline)) void small_resample(const SmallResample &st
 // their registers do not add to the sweep's.
 __device__ __attribute__((noinline)) void team_stats(const PostArgs &a, uint32_t *lds, uint64_t *scratch,
                                                      uint32_t lds_cap) {
-    post_stats<8, true>(a, lds, scratch, lds_cap);
+    post_energy<8, true>(a, lds, scratch, lds_cap);
+    __syncthreads();
+    post_magnet<8, true>(a, lds, scratch, lds_cap);
 }
 
 template <uint32_t LT, uint32_t GT, bool QSMALL, bool T64>

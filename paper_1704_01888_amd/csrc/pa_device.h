@@ -132,15 +132,16 @@ __host__ __device__ inline uint32_t scan_block(uint64_t n) {
     const uint64_t rows = (n + row * max_blocks - 1) / (row * max_blocks);
     return (uint32_t)(row * (rows ? rows : 1));
 }
+__host__ __device__ inline uint32_t scan_blocks(uint64_t n, uint32_t block) { return (uint32_t)((n + block - 1) / block); }
 // Workgroups of a post launch: statistics (of the energies; of M~ and the
 // digest, where asked for), the weight blocks, and the resampling workgroup of
 // a small population.
 __host__ __device__ inline uint32_t post_stats_blocks(const PostArgs &a) { return a.Mt || a.H ? 2u : 1u; }
 __host__ __device__ inline uint32_t post_blocks(const PostArgs &a) {
-    return post_stats_blocks(a) + (a.do_weights ? (uint32_t)((a.R_i + a.wblock - 1) / a.wblock) : 0u) + (a.small ? 1u : 0u);
+    return post_stats_blocks(a) + (a.do_weights ? scan_blocks(a.R_i, a.wblock) : 0u) + (a.small ? 1u : 0u);
 }
 __host__ __device__ inline uint32_t countfill_blocks(const SlotmapArgs &m) {
-    return (uint32_t)((m.R_prev + m.block - 1) / m.block);
+    return scan_blocks(m.R_prev, m.block);
 }
 
 // Lattices beyond one workgroup's LDS (L > 256): replicas stay in HBM; one
@@ -185,9 +186,12 @@ hipError_t launch_tiled_measure(const TiledArgs &a, hipStream_t s);
 hipError_t launch_tiled_finalize(const TiledArgs &a, hipStream_t s);
 
 hipError_t launch_sweep(const SweepArgs &a, hipStream_t s);
-hipError_t launch_post(const PostArgs &a, hipStream_t s);
+// scratch (16-byte aligned, for the launch alone): `scratch_words` words, for
+// the block histograms / sums of large populations
+hipError_t launch_post(const PostArgs &a, uint32_t *scratch, uint64_t scratch_words, hipStream_t s);
 // multinomial draws (k_sample), then count scan + slot map (k_countfill)
-hipError_t launch_resample(const SampleArgs &a, const SlotmapArgs &m, hipStream_t s);
+hipError_t launch_resample(const SampleArgs &a, const SlotmapArgs &m, uint64_t *scratch, uint64_t scratch_words,
+                           hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s);
 
 // One launch of many small fills and copies (a batch's start: zeroed

@@ -322,7 +322,8 @@ pa_status plan_layout(const pa_run_desc *d, Plan &p) {
     p.off_Hacc = o; o += (p.digest && p.tiled) ? align256(8 * p.R_cap) : 0;
     // second energy, M~ and digest-term buffers: the team launch alternates
     // them by step (the statistics of one step and the sweeps of the next run
-    // at the same time)
+    // at the same time); the energies' is also the scratch of post and count
+    // launches over large populations
     p.off_E2 = o; o += p.tiled ? 0 : align256(4 * p.R_cap);
     p.off_Mt2 = o; o += (!p.tiled && p.mag) ? align256(4 * p.R_cap) : 0;
     p.off_H2 = o; o += (!p.tiled && p.digest) ? align256(8 * p.R_cap) : 0;
@@ -529,9 +530,15 @@ pa::PostArgs post_args(pa_run_state *r, uint32_t i) {
     return s;
 }
 
+// Words of the second energy buffer, the launches' scratch: only a team launch
+// keeps energies there, and no launch of another kind is between its steps.
+uint64_t launch_scratch(const Plan &p) { return p.tiled ? 0u : p.R_cap; }
+
 pa_status launch_post_for(pa_run_state *r, uint32_t i) {
     const pa::PostArgs s = post_args(r, i);
-    return timed_launch(r, PA_KERNEL_POST, "post kernel", [&] { return pa::launch_post(s, r->stream); });
+    return timed_launch(r, PA_KERNEL_POST, "post kernel", [&] {
+        return pa::launch_post(s, r->at<uint32_t>(r->plan.off_E2), launch_scratch(r->plan), r->stream);
+    });
 }
 
 pa::SweepArgs sweep_args(pa_run_state *r, uint32_t i, uint32_t mode, const uint8_t *old_pop,
@@ -698,7 +705,7 @@ pa_status do_step(pa_run_state *r) {
         pa::SlotmapArgs m;
         resample_args(r, i, R_prev, R_new, s, m);
         if ((st = timed_launch(r, PA_KERNEL_RESAMPLE, "resample kernel",
-                               [&] { return pa::launch_resample(s, m, r->stream); })))
+                               [&] { return pa::launch_resample(s, m, r->at<uint64_t>(p.off_E2), launch_scratch(p), r->stream); })))
             return st;
         anc = m.anc;
     } else if (R_new != R_prev) {

@@ -6,15 +6,17 @@
 //                    theta checkerboard Metropolis sweeps (step 3) held in LDS,
 //                    then the energy of eq. (3) (and M~ of eq. (5)) per replica.
 //   k_tiled_*      : the same for lattices beyond one workgroup's LDS, in HBM.
-//   k_post         : workgroup 0: the energy (and M~) histograms from the
-//                    per-replica values, population sums for eq. (4), the
-//                    reference energy and ln Q of step 2 / eq. (2) in FP64,
-//                    histogram widths (Sec. 4); workgroups 1, 2, ...: the
+//   k_post         : workgroup 0: the energy histogram from the per-replica
+//                    values, population sums for eq. (4), the reference energy
+//                    and ln Q of step 2 / eq. (2) in FP64, the histogram's width
+//                    (Sec. 4); one more for M~ and the digest; the others: the
 //                    integer weights W(|E_j - E_ref|) of the next resampling
-//                    and their scan, one block of replicas each.
+//                    and their scan, one block of replicas each.  For large
+//                    populations from the blocks' histograms (k_chunk_hist).
 //   k_sample       : the multinomial draws of the resampling step.
 //   k_countfill    : exclusive scan of the copy numbers -> ancestor of each new
-//                    slot, one block of ancestors per workgroup.
+//                    slot, one block of ancestors per workgroup (large
+//                    populations: after k_count_sums).
 //   *_batch        : the same for several runs in one launch.
 //
 // A replica held in LDS is updated by G lanes: part of a wave (small L), one
@@ -964,6 +966,9 @@ __device__ void store_hist(const HistView &v, uint32_t *out) {
 
 constexpr uint32_t POST_LDS_BINS = 14336;   // 56 KB window for the histograms in LDS
 
+// Populations above these take block histograms / sums (see post_chunks).
+constexpr uint64_t CHUNKS_MIN_R = 65536, COUNT_SUMS_MIN_R = 65536;
+
 constexpr uint32_t SHORT_RUN = 8;   // copies written by their own lane in the slot map
 
 // Multi-workgroup scans: workgroup b of a launch takes the elements
@@ -974,12 +979,11 @@ constexpr uint32_t SHORT_RUN = 8;   // copies written by their own lane in the s
 // no communication.
 
 // C_j = sum_{j' <= j} wf(E_j') for first <= j < last (E 16-byte aligned, C
-// 32-byte aligned, first a multiple of 4).
+// 32-byte aligned, first a multiple of 4); each thread brings a part of the
+// sum before the block, `carry`.
 template <typename WF>
 __device__ __forceinline__ void weight_block(const int32_t *E, uint32_t first, uint32_t last, WF wf,
-                                             uint64_t *C, uint64_t *scratch) {
-    uint64_t carry = 0;
-    for_each_tiled(E, first, [&](int32_t e) { carry += wf(e); });
+                                             uint64_t *C, uint64_t *scratch, uint64_t carry) {
     carry = block_reduce(carry, [](uint64_t x, uint64_t y) { return x + y; }, scratch);
     __syncthreads();
     for (uint32_t base = first; base < last; base += blockDim.x * 4u) {
@@ -1026,11 +1030,62 @@ __device__ __forceinline__ void weight_block(const int32_t *E, uint32_t first, u
 // that chain was the longest: 32x32, R = 1e4, with widths 21.7 -> 12.6 us; four
 // 64x64 runs of R = 1e3 27.8 -> 17.9 us.
 // ---------------------------------------------------------------------------
+// Large populations (post_chunks): a launch before k_post forms the energy
+// histogram of each block of a.wblock replicas, chunks[block][level].  The
+// statistics workgroup adds them up and each weight workgroup takes the range
+// and the sum before its block from them, so none of them reads the whole
+// population (us of the launches): 16x16, R = 1e6 106 -> 28.6; R = 2e5 27.6 ->
+// 17.1; 32x32, R = 4e5 47.8 -> 21.8.
+//
+// Block c's record: the first and last level that occur, then the counts of the
+// levels between them.
+__host__ __device__ inline uint32_t chunk_stride(uint32_t nb) { return nb + 2u; }
+
+// f(c, level, count) for every level within block c's range, c < n; a wave
+// takes every 16th block.  Only the ranges are read: a few hundred of the
+// thousands of levels.
+template <typename F>
+__device__ __forceinline__ void each_chunk_count(const uint32_t *h, uint32_t n, uint32_t nb, F f) {
+    const uint32_t lane = threadIdx.x & 63u;
+    for (uint32_t c = threadIdx.x >> 6; c < n; c += WG_WAVES) {
+        const uint32_t *hc = h + (size_t)c * chunk_stride(nb);
+        const uint32_t lo = hc[0], hi = hc[1];
+#pragma unroll 4
+        for (uint32_t b = lo + lane; b <= hi; b += 64u) f(c, b, hc[2u + b - lo]);
+    }
+}
+// The range of levels of the whole population.
+__device__ __forceinline__ SumMinMax chunk_range(const uint32_t *h, uint32_t n, uint32_t nb) {
+    int32_t mn = 0x7fffffff, mx = (int32_t)0x80000000;
+    for (uint32_t c = threadIdx.x; c < n; c += blockDim.x) {
+        mn = min(mn, (int32_t)h[(size_t)c * chunk_stride(nb)]);
+        mx = max(mx, (int32_t)h[(size_t)c * chunk_stride(nb) + 1u]);
+    }
+    return block_sum_min_max(0, mn, mx);
+}
+
+// The energy histogram of the whole population in lds[nbins] (as build_hist
+// returns it), from its blocks' histograms.
+__device__ __forceinline__ HistBuild sum_chunks(const PostArgs &a, const uint32_t *chunks, uint32_t *lds) {
+    for (uint32_t b = threadIdx.x; b < a.nbins; b += blockDim.x) lds[b] = 0u;
+    __syncthreads();
+    int64_t sum = 0;
+    int32_t mn = 0x7fffffff, mx = (int32_t)0x80000000;
+    each_chunk_count(chunks, scan_blocks(a.R_i, a.wblock), a.nbins, [&](uint32_t, uint32_t b, uint32_t x) {
+        if (!x) return;
+        atomicAdd(&lds[b], x);
+        const int32_t e = (int32_t)b - a.two_n;
+        sum += (int64_t)x * e; mn = min(mn, e); mx = max(mx, e);
+    });
+    const SumMinMax t = block_sum_min_max(sum, mn, mx);
+    return HistBuild{HistView{lds, 0u, a.nbins, a.nbins}, t.sum, t.mn, t.mx};
+}
+
 // V: values per thread and load round of the population passes (the team
 // kernel's smaller populations take fewer, and fewer registers).
 template <uint32_t V = 32, bool LEAN = false>
 __device__ __forceinline__ void post_energy(const PostArgs &a, uint32_t *lds_hist, uint64_t *scratch,
-                                            uint32_t lds_cap = POST_LDS_BINS) {
+                                            uint32_t lds_cap = POST_LDS_BINS, const uint32_t *chunks = nullptr) {
     __shared__ double s_w[WG_WAVES];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
     const uint32_t nb = a.nbins;
@@ -1039,7 +1094,8 @@ __device__ __forceinline__ void post_energy(const PostArgs &a, uint32_t *lds_his
     const double mbF_i = (tid == 0 && a.has_next) ? a.mbF[a.step] : 0.0;
 
     // eq. (4) sums and the energy histogram h[E + 2N] of step i
-    const HistBuild he = build_hist<V, LEAN>(a.E, a.R_i, a.two_n, nb, lds_hist, lds_cap, a.hist);
+    const HistBuild he = chunks ? sum_chunks(a, chunks, lds_hist)
+                                : build_hist<V, LEAN>(a.E, a.R_i, a.two_n, nb, lds_hist, lds_cap, a.hist);
     const int32_t ref = a.dbeta_next >= 0.0 ? he.mn : he.mx;   // E_ref of step i+1
     if (tid == 0) {
         a.E_sum[a.step] = he.sum;
@@ -1210,7 +1266,11 @@ __device__ __forceinline__ void post_weights(const PostArgs &a, uint32_t b, uint
     const int32_t ref = a.dbeta_next >= 0.0 ? t.mn : t.mx;
     const auto weights = [&](auto wf) {
         if (in_regs) weight_row_regs(tr, b, wf, a.C, scratch);
-        else weight_block(a.E, first, last, wf, a.C, scratch);
+        else {
+            uint64_t carry = 0;
+            for_each_tiled(a.E, first, [&](int32_t e) { carry += wf(e); });
+            weight_block(a.E, first, last, wf, a.C, scratch, carry);
+        }
     };
     if (a.w_const) {
         const uint64_t wc = a.w_const;
@@ -1237,6 +1297,37 @@ __device__ __forceinline__ void post_weights(const PostArgs &a, uint32_t b, uint
     }
 }
 
+// The same from the blocks' histograms: the sum before block b is that of the
+// blocks' counts times their weights, which LDS holds (the levels that occur).
+__device__ __forceinline__ void post_weights_chunks(const PostArgs &a, uint32_t b, uint32_t *lds, uint64_t *scratch,
+                                                    const uint32_t *chunks) {
+    const uint32_t n = (uint32_t)a.R_i, tid = threadIdx.x;
+    const uint32_t first = b * a.wblock, last = min(first + a.wblock, n);
+    uint64_t *Wl = reinterpret_cast<uint64_t *>(lds);
+    SumMinMax t = chunk_range(chunks, scan_blocks(n, a.wblock), a.nbins);
+    t.mn -= a.two_n;
+    t.mx -= a.two_n;
+    const int32_t ref = a.dbeta_next >= 0.0 ? t.mn : t.mx;
+    if (a.w_const) {
+        const uint64_t wc = a.w_const;
+        weight_block(a.E, first, last, [=](int32_t) { return wc; }, a.C, scratch, tid == 0 ? first * wc : 0ull);
+        return;
+    }
+    const uint32_t span = (uint32_t)(t.mx - t.mn) + 1u;
+    const uint32_t nW = a.D < span ? a.D : span;
+    for (uint32_t d = tid; d < nW; d += blockDim.x) Wl[d] = a.W[d];
+    __syncthreads();
+    const auto wf = [=](int32_t e) {
+        const uint32_t d = (uint32_t)abs(e - ref);
+        return d < nW ? Wl[d] : 0ull;
+    };
+    uint64_t carry = 0;
+    each_chunk_count(chunks, b, a.nbins, [&](uint32_t, uint32_t i, uint32_t x) {
+        carry += x * wf((int32_t)i - a.two_n);
+    });
+    weight_block(a.E, first, last, wf, a.C, scratch, carry);
+}
+
 __device__ __forceinline__ void small_resample_body(const SmallResample &st, uint32_t *ancL, uint32_t *ru,
                                                     uint64_t *C, uint64_t *scratch, bool write_out);
 
@@ -1261,6 +1352,27 @@ __device__ __forceinline__ void post_block(const PostArgs &a, uint32_t b) {
 
 __global__ void __launch_bounds__(WG_THREADS) k_post(PostArgs a) { post_block(a, blockIdx.x); }
 
+// The energy histogram of block blockIdx.x, then the post launch that reads
+// these (post_chunks).
+__global__ void __launch_bounds__(WG_THREADS) k_chunk_hist(PostArgs a, uint32_t *chunks) {
+    __shared__ __align__(16) uint32_t lds[POST_LDS_BINS];
+    const uint64_t first = (uint64_t)blockIdx.x * a.wblock, n = min((uint64_t)a.wblock, a.R_i - first);
+    const HistBuild h = build_hist(a.E + first, n, a.two_n, a.nbins, lds, POST_LDS_BINS, nullptr);
+    __syncthreads();
+    uint32_t *out = chunks + (size_t)blockIdx.x * chunk_stride(a.nbins);
+    const uint32_t lo = (uint32_t)(h.mn + a.two_n), hi = (uint32_t)(h.mx + a.two_n);
+    if (threadIdx.x == 0) { out[0] = lo; out[1] = hi; }
+    for (uint32_t b = lo + threadIdx.x; b <= hi; b += blockDim.x) out[2u + b - lo] = h.v.h[b];
+}
+__global__ void __launch_bounds__(WG_THREADS) k_post_chunks(PostArgs a, const uint32_t *chunks) {
+    __shared__ __align__(16) uint32_t lds[POST_LDS_BINS];
+    __shared__ uint64_t scratch[17];
+    const uint32_t stats = post_stats_blocks(a);
+    if (blockIdx.x == 0) post_energy(a, lds, scratch, POST_LDS_BINS, chunks);
+    else if (blockIdx.x < stats) post_magnet(a, lds, scratch);
+    else post_weights_chunks(a, blockIdx.x - stats, lds, scratch, chunks);
+}
+
 // Batched form: run r owns workgroups start[r] .. start[r+1]-1.
 __global__ void __launch_bounds__(WG_THREADS) k_post_batch(const PostArgs *runs, const uint32_t *start, uint32_t n) {
     const uint32_t r = segment_of(start, n, blockIdx.x);
@@ -1274,7 +1386,9 @@ __global__ void __launch_bounds__(WG_THREADS) k_post_batch(const PostArgs *runs,
 // order, eq. (1)) for the ancestors j of block b; the other parity's counts
 // are cleared for the next step.
 // ---------------------------------------------------------------------------
-__device__ void countfill_block(const SlotmapArgs &a, uint32_t b, uint64_t *scratch) {
+// `sums`: the blocks' sums of the counts, or nullptr: every workgroup adds up
+// the counts before its block itself.
+__device__ void countfill_block(const SlotmapArgs &a, uint32_t b, uint64_t *scratch, const uint64_t *sums) {
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t n = (uint32_t)a.R_prev;   // R_prev < 2^32
     const uint32_t first = b * a.block, last = min(first + a.block, n);
@@ -1303,7 +1417,11 @@ __device__ void countfill_block(const SlotmapArgs &a, uint32_t b, uint64_t *scra
     // (tiles of 16 per thread: the counts were just written by atomics, and
     // the deeper tiles of 32 measured slower here, 6.7 against 5.9 us at
     // R = 2e4 and 123 against 115 us at R = 2e5)
-    for_each_tiled<16>(a.r, first, [&](uint32_t c) { carry += c; });
+    if (sums) {
+        for (uint32_t c = tid; c < b; c += blockDim.x) carry += sums[c];
+    } else {
+        for_each_tiled<16>(a.r, first, [&](uint32_t c) { carry += c; });
+    }
     carry = block_reduce(carry, [](uint64_t x, uint64_t y) { return x + y; }, scratch);
     __syncthreads();
     for (uint32_t base = first; base < last; base += blockDim.x * 4u) {
@@ -1419,9 +1537,19 @@ __global__ void __launch_bounds__(256) k_sample_batch(const SampleArgs *runs, co
     sample_one(a, (uint64_t)(blockIdx.x - start[r]) * blockDim.x + threadIdx.x);
 }
 
-__global__ void __launch_bounds__(WG_THREADS) k_countfill(SlotmapArgs m) {
+__global__ void __launch_bounds__(WG_THREADS) k_countfill(SlotmapArgs m, const uint64_t *sums) {
     __shared__ uint64_t scratch[17];
-    countfill_block(m, blockIdx.x, scratch);
+    countfill_block(m, blockIdx.x, scratch, sums);
+}
+
+// Sum of the counts of block blockIdx.x.
+__global__ void __launch_bounds__(WG_THREADS) k_count_sums(SlotmapArgs m, uint64_t *sums) {
+    __shared__ uint64_t scratch[17];
+    const uint64_t first = (uint64_t)blockIdx.x * m.block, n = min((uint64_t)m.block, m.R_prev - first);
+    uint64_t sum = 0;
+    for_each_tiled<16>(m.r + first, n, [&](uint32_t c) { sum += c; });
+    sum = block_reduce(sum, [](uint64_t x, uint64_t y) { return x + y; }, scratch);
+    if (threadIdx.x == 0) sums[blockIdx.x] = sum;
 }
 
 // Batched form: run r owns workgroups start[r] .. start[r+1]-1.
@@ -1430,7 +1558,7 @@ __global__ void __launch_bounds__(WG_THREADS) k_countfill_batch(const SlotmapArg
     __shared__ uint64_t scratch[17];
     const uint32_t r = segment_of(start, n, blockIdx.x);
     const SlotmapArgs m = runs[r];
-    countfill_block(m, blockIdx.x - start[r], scratch);
+    countfill_block(m, blockIdx.x - start[r], scratch, nullptr);
 }
 
 __global__ void k_fill_u32(uint32_t *p, uint64_t n, uint32_t v) {
@@ -2256,15 +2384,40 @@ hipError_t launch_sweep(const SweepArgs &args, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_post(const PostArgs &a, hipStream_t s) {
+// Whether a post launch works from block histograms, and a count scan from
+// block sums: where the second launch costs less than the passes over the whole
+// population that it saves.  Measured, without and with (us; sides 8, 16, 32):
+// post at R = 33000 12.2 12.0 12.0 / 13.5 13.7 14.8, 50000 13.4 13.5 13.6 / 13.9
+// 14.0 15.0, 70000 15.2 15.2 15.1 / 14.1 14.5 15.0, 100000 18.4 18.2 18.2 / 14.9
+// 15.3 15.9; draws and count scan at 50000 15.5 15.3 15.9 / 16.3 15.9 16.4,
+// 70000 17.2 17.1 18.1 / 17.2 17.1 17.9, 100000 20.1 19.5 20.2 / 18.5 18.3 19.7,
+// 1e6 125.7 129.1 / 93.9 97.0.  The weights of all levels fit LDS, and the
+// blocks' records the scratch.
+bool post_chunks(const PostArgs &a, uint64_t scratch_words) {
+    return a.do_weights && a.R_i > CHUNKS_MIN_R && a.nbins <= POST_LDS_BINS / 2u &&
+           (uint64_t)scan_blocks(a.R_i, a.wblock) * chunk_stride(a.nbins) <= scratch_words;
+}
+bool count_sums(const SlotmapArgs &m, uint64_t scratch_words) {
+    return m.R_prev > COUNT_SUMS_MIN_R && 2ull * countfill_blocks(m) <= scratch_words;
+}
+
+hipError_t launch_post(const PostArgs &a, uint32_t *chunks, uint64_t scratch_words, hipStream_t s) {
+    if (post_chunks(a, scratch_words)) {
+        hipLaunchKernelGGL(k_chunk_hist, dim3(scan_blocks(a.R_i, a.wblock)), dim3(WG_THREADS), 0, s, a, chunks);
+        hipLaunchKernelGGL(k_post_chunks, dim3(post_blocks(a)), dim3(WG_THREADS), 0, s, a, (const uint32_t *)chunks);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_post, dim3(post_blocks(a)), dim3(WG_THREADS), 0, s, a);
     return hipGetLastError();
 }
 
-hipError_t launch_resample(const SampleArgs &a, const SlotmapArgs &m, hipStream_t s) {
+hipError_t launch_resample(const SampleArgs &a, const SlotmapArgs &m, uint64_t *sums, uint64_t scratch_words,
+                           hipStream_t s) {
     const uint64_t blocks = (a.n_new + 255) / 256;
     if (blocks) hipLaunchKernelGGL(k_sample, dim3((uint32_t)blocks), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_countfill, dim3(countfill_blocks(m)), dim3(WG_THREADS), 0, s, m);
+    if (!count_sums(m, scratch_words)) sums = nullptr;
+    if (sums) hipLaunchKernelGGL(k_count_sums, dim3(countfill_blocks(m)), dim3(WG_THREADS), 0, s, m, sums);
+    hipLaunchKernelGGL(k_countfill, dim3(countfill_blocks(m)), dim3(WG_THREADS), 0, s, m, (const uint64_t *)sums);
     return hipGetLastError();
 }
 

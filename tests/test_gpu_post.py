@@ -49,3 +49,31 @@ def test_outputs_of_a_post_launch(ctx, R, resample):
     got = pa.pa_run_batch(ctx, [pa.Desc(outputs=o | pa.OUT_FINAL, **kw) for kw, o in zip(runs, OUTPUTS)])
     for g, w in zip(got, want):
         _compare(g, w)
+
+
+LARGE = [
+    # Poisson populations on both sides of the size from which the post and count
+    # launches work from block histograms and sums (65536); one block of one replica
+    dict(L=8, q=4, R=65536, beta=linear_betas(1.2, 12), theta=1, seed=5, resample=0),
+    dict(L=4, q=3, R=65537, beta=linear_betas(1.2, 3), theta=1, seed=6, resample=1),
+    # equal weights (a repeated beta), strongly skewed ones, and none
+    dict(L=8, q=3, R=70001, beta=np.array([0.0, 0.0, 0.5, 1.5, 3.0]), theta=1, seed=7, resample=1),
+    dict(L=8, q=3, R=70001, beta=linear_betas(1.2, 3), theta=1, seed=8, resample=2),
+    # heating from ground states: one level at first, weights from the largest energy
+    dict(L=12, q=6, R=80002, beta=np.array([1.6, 1.3, 1.0, 0.7]), theta=1, seed=9, resample=1, init=pa.INIT_GROUND),
+    # the largest side whose blocks fit the scratch, and the next
+    dict(L=44, q=10, R=66000, beta=linear_betas(0.9, 2), theta=1, seed=10, resample=0),
+    dict(L=46, q=10, R=66000, beta=linear_betas(0.9, 2), theta=1, seed=11, resample=0),
+    # several rows a block
+    dict(L=8, q=5, R=270003, beta=linear_betas(1.4, 3), theta=1, seed=12, resample=0),
+]
+
+
+@pytest.mark.parametrize("kw", LARGE, ids=lambda c: f"L{c['L']}R{c['R']}r{c['resample']}")
+def test_populations_with_block_histograms(ctx, kw):
+    outs = OUTPUTS[-1]
+    print(f"\nL={kw['L']} q={kw['q']} R={kw['R']} resample={kw['resample']}", flush=True)
+    want = _oracle(kw, outs)
+    _compare(pa.pa_run(ctx, pa.Desc(outputs=outs | pa.OUT_FINAL, **kw)), want)
+    if kw["R"] == 65536:
+        assert (want["R_i"] > 65536).any() and (want["R_i"] <= 65536).any()

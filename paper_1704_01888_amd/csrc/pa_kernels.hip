@@ -1373,8 +1373,12 @@ __global__ void __launch_bounds__(WG_THREADS) k_post_chunks(PostArgs a, const ui
     else post_weights_chunks(a, blockIdx.x - stats, lds, scratch, chunks);
 }
 
-// Batched form: run r owns workgroups start[r] .. start[r+1]-1.
-__global__ void __launch_bounds__(WG_THREADS) k_post_batch(const PostArgs *runs, const uint32_t *start, uint32_t n) {
+// Batched form: run r owns workgroups start[r] .. start[r+1]-1.  `runs` is
+// restrict: the record then stays in scalar registers (read through memory
+// that stores might change it took vector registers, 83 of them spilled: 20
+// runs of 8x8, R = 1e3, 11.4 us instead of 8.7).
+__global__ void __launch_bounds__(WG_THREADS) k_post_batch(const PostArgs *__restrict__ runs,
+                                                           const uint32_t *start, uint32_t n) {
     const uint32_t r = segment_of(start, n, blockIdx.x);
     const PostArgs a = runs[r];
     post_block(a, blockIdx.x - start[r]);

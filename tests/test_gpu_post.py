@@ -77,3 +77,11 @@ def test_populations_with_block_histograms(ctx, kw):
     _compare(pa.pa_run(ctx, pa.Desc(outputs=outs | pa.OUT_FINAL, **kw)), want)
     if kw["R"] == 65536:
         assert (want["R_i"] > 65536).any() and (want["R_i"] <= 65536).any()
+
+
+@pytest.mark.parametrize("R", [1, 2, 3, 5, 33, 34, 2999, 3500])
+def test_small_resampling_with_skewed_weights(ctx, R):
+    """Draws outside the search window; populations that fill no load of four."""
+    kw = dict(L=8, q=3, R=R, beta=np.array([0.0, 0.0, 0.5, 1.5, 3.0, 2.0]), theta=1, seed=70 + R, resample=1)
+    print(f"\nR={R}", flush=True)
+    _compare(pa.pa_run(ctx, pa.Desc(outputs=OUTPUTS[-1] | pa.OUT_FINAL, **kw)), _oracle(kw, OUTPUTS[-1]))

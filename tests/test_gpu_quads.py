@@ -164,3 +164,18 @@ def test_launch_of_several_and_single_replicas_per_lane(ctx, L, G, w, R):
         want = oracle.run(oracle.Desc(**r), final=True, hist=True, magnetisation=True, digest=True)
         for key in KEYS:
             assert (g[key] == want[key]).all(), (key, r["R"])
+
+
+def test_batch_takes_the_shape_of_its_replicas_together(ctx):
+    """Small runs of one side in one batch sweep with the tuned shape of their
+    total population: quad and dword runs, 64-bit thresholds in the middle, M~."""
+    for L, one, many in ((8, (16, 2), (8, 4)), (24, (48, 3), (24, 12))):
+        for r_class in range(4):
+            ctx.tune_set(L, 0, r_class, *(many if r_class else one))
+    runs = [dict(L=L, q=q, R=1001 + q, beta=linear_betas(b, 4), theta=2, seed=300 + q + L, resample=1)
+            for L in (8, 24) for q, b in ((8, 1.2), (20, 1.2), (33, 1.2), (5, 6.0))]
+    got = pa.pa_run_batch(ctx, [pa.Desc(outputs=ALL, **r) for r in runs])
+    for r, g in zip(runs, got):
+        want = oracle.run(oracle.Desc(**r), final=True, hist=True, magnetisation=True, digest=True)
+        for key in KEYS:
+            assert (g[key] == want[key]).all(), (key, r["L"], r["q"])

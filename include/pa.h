@@ -433,8 +433,8 @@ pa_status pa_free_energy_crossing(const double *beta, const double *mbf_cool, co
  * a stream of one kind (eight independent chains per lane, 32 waves per
  * compute unit) on every compute unit of the context's device and returns the
  * rate in lane-instructions per second (the fastest of three timed launches
- * after a warm-up).  PA_PROBE_MIX is the sweep inner loop's mix of kinds per
- * pair update (18 multiply-adds, 19 three-input bitops, 4 each of perm, xad
+ * after a warm-up).  PA_PROBE_MIX is the inner loop's mix of kinds per pair
+ * update of the sweep kernel that serves q > 32 (18 multiply-adds, 19 three-input bitops, 4 each of perm, xad
  * and sad, 2 xor, 2 and, 2 compare-select pairs).  d_out is a device buffer of
  * at least 4 * 256 * 8 * (compute units) bytes (one word per probe thread,
  * overwritten); the launches are ordered on `stream` and the call waits for
@@ -448,7 +448,7 @@ enum {
     PA_PROBE_XAD = 5,     /* v_xad_u32                               */
     PA_PROBE_MULHI = 6,   /* v_mul_hi_u32                            */
     PA_PROBE_CMPSEL = 7,  /* v_cmp_le_u32 to VCC + v_cndmask_b32     */
-    PA_PROBE_MIX = 8,     /* the sweep's mix, see above              */
+    PA_PROBE_MIX = 8,     /* a sweep's mix, see above                */
     PA_PROBE_KINDS = 9
 };
 pa_status pa_issue_probe(pa_ctx *ctx, uint32_t kind, void *d_out, uint64_t out_bytes, void *stream,

@@ -347,8 +347,9 @@ pa_status pa_plan_batch(const pa_run_desc *descs, uint32_t n, uint64_t *workspac
 pa_status pa_ctx_set_graphs(pa_ctx *ctx, int enable);
 /* Batch modes.  PA_BATCH_SEGMENTED (the default): the launches above, one
  * set per global step.  PA_BATCH_TEAM: the runs whose every remaining step fits
- * one workgroup's sweep class, with populations up to 8192 replicas and no
- * 64-bit thresholds, go through all their steps in one cooperative launch per
+ * one workgroup's sweep class, with populations up to 8192 replicas, no
+ * 64-bit thresholds and no tuned shape that only the four-site kernel has
+ * (below), go through all their steps in one cooperative launch per
  * sweep class and workgroup size -- each run a team of workgroups that meet
  * at one device-wide barrier per step: every sweeping workgroup redoes the
  * resampling of eq. (1) from the energies in its LDS and then claims blocks of

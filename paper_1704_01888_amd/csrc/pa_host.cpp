@@ -2130,10 +2130,13 @@ constexpr uint64_t kTeamTimeoutTicks = 1000000000ull;   // 10 s of the 100 MHz c
 
 // The class of a run's sweeps if every step of it can go to a team launch,
 // else 0 (tiled, byte-kernel or 64-bit-threshold steps, a population above
-// kTeamRMax, or no team kernel for the class).
+// kTeamRMax, no team kernel for the class, or a shape that only the quad kernel
+// has: the team kernel sweeps as the dword kernel does, whose replicas of more
+// than 64 lanes take a whole group).
 uint32_t team_class(const pa_run_state *r) {
     const Plan &p = r->plan;
     if (p.tiled || p.R_cap > kTeamRMax || r->step + 1 >= p.desc.K) return 0;
+    if (pa::quad_only(p.desc.L, r->G, r->wpb) || pa::team_threads() % (64u * r->wpb) != 0) return 0;
     for (uint32_t i = r->step + 1; i < p.desc.K; ++i)
         if (p.T[(size_t)i * 4 + 3] == 0) return 0;
     const uint32_t cls = pa::sweep_class(p.desc.L, p.desc.q, false, r->G);

@@ -166,3 +166,27 @@ def test_abort_from_another_thread_cancels_and_the_context_stays_usable(ctx):
     assert ctx.batch_info()[0] == 3
     for d, g in zip(descs, got):
         _same(g, pa.pa_run(ctx, d))
+
+
+def test_shapes_that_only_the_quad_kernel_has_go_segmented():
+    """Lanes of a team class in workgroups of several replicas, which the team
+    kernel's sweeps do not have: such runs leave the team launch."""
+    c = pa.Context(0, tune_cache=False)
+    try:
+        c.set_batch_mode(pa.BATCH_TEAM)
+        shapes = {32: [(128, w) for w in (4, 8, 12, 16)], 64: [(512, 16)]}
+        for L, R in ((32, 300), (64, 130)):
+            cases = [dict(L=L, q=q, R=R + q, beta=linear_betas(1.2, 6), theta=2, seed=80 + q, resample=1)
+                     for q in (10, 20, 40)]
+            descs = [pa.Desc(outputs=ALL, **k) for k in cases]
+            want = [oracle.run(oracle.Desc(**k), hist=True, final=True, digest=True, magnetisation=True) for k in cases]
+            for G, w in shapes[L]:
+                c.tune_set(L, 0, 0, G, w)
+                print(f"\nL={L} lanes={G} waves={w}", flush=True)
+                got = pa.pa_run_batch(c, descs)
+                assert c.batch_info() == (0, 0)
+                for g, x in zip(got, want):
+                    for key in ("R_i", "final_spins", "final_E", "last_anc", "hist", "Mt_sum", "mhist", "digest"):
+                        assert (g[key] == x[key]).all(), key
+    finally:
+        c.close()

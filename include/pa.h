@@ -202,11 +202,16 @@ pa_status pa_ctx_get_lanes(pa_ctx *ctx, uint32_t L, uint32_t *lanes, uint32_t *c
 pa_status pa_autotune(pa_ctx *ctx, uint32_t L, uint32_t q, void *d_ws, uint64_t ws_bytes, void *stream,
                       uint32_t *best_lanes, double *best_attempts_per_ns);
 
-/* Tuned sweep shapes.  An entry gives, for lattice side L, a q class (q_large:
- * q above 128, the other form of the neighbour comparison) and a population
- * class (r_class: R_cap below 2^11, 2^14, 2^17, or above), the lanes per
- * replica and the waves per workgroup of the sweep kernel.  Later runs on the
- * context whose description falls in an entry's class sweep with its shape --
+/* Tuned sweep shapes.  An entry gives, for lattice side L, a kernel class
+ * (q_large: 0 for q up to 128, 1 for q above 128, 2 for the runs and steps with
+ * q up to 128 that the four-site kernel does not take: q above 32, steps with
+ * 64-bit thresholds, loaded populations with states beyond q, and team
+ * launches) and a population class (r_class: R_cap below 2^11, 2^14, 2^17, or
+ * above), the lanes per replica and the waves per workgroup of the sweep kernel.
+ * An entry of class 0 serves class 2 as well, where its shape is not one that
+ * only the four-site kernel has, until an entry of class 2 is installed after it
+ * or timed.  Later runs on the context whose description falls in an entry's class
+ * sweep with its shape --
  * pa_run, pa_run_batch and the serving loop alike -- unless pa_ctx_set_lanes
  * fixed a lane count for L; results do not depend on the shape.  Lattices on
  * the tiled path (L > 256) have no shape.
@@ -214,11 +219,13 @@ pa_status pa_autotune(pa_ctx *ctx, uint32_t L, uint32_t q, void *d_ws, uint64_t 
  *   each, the waves per workgroup that fit 1024 threads, 256 for L = 2 mod 4,
  *   and the LDS) on a synthetic run of R replicas (K = 3, theta = 10) in the
  *   caller's workspace (at least pa_plan's size for that run), keeps the
- *   fastest as the entry of (L, q, R)'s class and returns it with its rate;
+ *   fastest as the entry of (L, q, R)'s class (q_large 0 for q up to 32, 2 up
+ *   to 128, 1 above) and returns it with its rate;
  *   `timed` (may be NULL) receives up to timed_cap of the shapes with their
  *   rates, *n_timed the number of shapes timed.  Calls on the context must
  *   not overlap it.
- * pa_tune_set: installs an entry (PA_ERR_INVALID if it is not a shape of L).
+ * pa_tune_set: installs an entry (PA_ERR_INVALID if it is not a shape of L in
+ *   its class; the four-site kernel's own shapes are of class 0).
  * pa_tune_get: the shape later runs of (L, q, R) will use (the entry, or the
  *   default with attempts_per_ns 0).
  * pa_tune_save / pa_tune_load: the context's entries as a text file, one JSON

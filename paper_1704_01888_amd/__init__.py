@@ -327,7 +327,8 @@ class Context:
         return out
 
     def tune_set(self, L: int, q_large: int, r_class: int, lanes: int, waves_per_block: int):
-        """Install a tuned shape for a class (pa_tune_set)."""
+        """Install a tuned shape for a class (pa_tune_set); q_large: 0 for q up
+        to 128, 1 above, 2 for what the four-site kernel does not take."""
         e = TuneEntry(int(L), int(q_large), int(r_class), int(lanes), int(waves_per_block), 0.0)
         _check(lib().pa_tune_set(self.handle, ctypes.byref(e)))
 

@@ -185,7 +185,10 @@ hipError_t launch_tiled_measure(const TiledArgs &a, hipStream_t s);
 // the same where the sums are complete (counted by the last sweep launch)
 hipError_t launch_tiled_finalize(const TiledArgs &a, hipStream_t s);
 
-hipError_t launch_sweep(const SweepArgs &a, hipStream_t s);
+// A sweep shape: lanes per replica, waves per workgroup.
+struct SweepShape { uint32_t lanes, waves_per_block; };
+// (dword: the run's shape where the quad kernel does not take the step)
+hipError_t launch_sweep(const SweepArgs &a, SweepShape dword, hipStream_t s);
 // scratch (16-byte aligned, for the launch alone): `scratch_words` words, for
 // the block histograms / sums of large populations
 hipError_t launch_post(const PostArgs &a, uint32_t *scratch, uint64_t scratch_words, hipStream_t s);
@@ -279,6 +282,9 @@ void dword_shape(uint32_t L, uint32_t lanes, uint32_t *G, uint32_t *waves_per_bl
 // q_counters: q when the sweep counts states for M~ (eq. (5)), else 0
 size_t sweep_lds_bytes(uint32_t N, uint32_t G, uint32_t waves_per_block, uint32_t q_counters);
 uint64_t replicas_per_block(uint32_t G, uint32_t waves_per_block);
+// Whether the quad kernel takes a run's step: q <= 32, 32-bit thresholds, no
+// loaded spins beyond q.
+bool quad_step(const SweepArgs &a);
 // Quad kernel (pa_quad.h): the most replicas per lane it has for a run's shape
 // (0: the run does not take it), its lane counts for L (up to 2), whether only
 // it has the shape.
@@ -288,7 +294,7 @@ bool quad_only(uint32_t L, uint32_t G, uint32_t waves_per_block);
 // LDS of a workgroup of a shape, whichever kernel takes it.
 size_t shape_lds_bytes(uint32_t L, uint32_t q, uint32_t G, uint32_t waves_per_block, uint32_t q_counters);
 struct SweepLaunch { uint32_t cls, blocks; uint64_t per_block; size_t lds; };
-uint32_t settle_sweep(SweepArgs &a, uint64_t replicas);
+uint32_t settle_sweep(SweepArgs &a, SweepShape dword, uint64_t replicas);
 // Of the `replicas` of a quad launch, those to be held one per lane (the last).
 uint64_t quad_singles(const SweepArgs &a, uint32_t nr, uint64_t replicas);
 SweepLaunch sweep_launch(const SweepArgs &a, uint32_t nr);

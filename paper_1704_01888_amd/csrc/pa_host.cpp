@@ -357,7 +357,7 @@ struct pa_ctx {
     uint32_t *team_abort;   // pinned host word read by the team launches' barrier waits
     std::atomic<int> abort_requested;
     uint32_t team_runs, team_launches;   // of the last pa_run_batch
-    // tuned sweep shapes by (L, q above 128, population class); guarded by
+    // tuned sweep shapes by (L, kernel class, population class); guarded by
     // tune_mu (the serving thread reads them too); tune_gen counts changes
     std::mutex tune_mu;
     std::map<uint64_t, pa_tune_entry> tune;
@@ -395,8 +395,35 @@ static uint8_t *ctx_staging(pa_ctx *c, size_t bytes, hipStream_t s) {
 static uint32_t r_class_of(uint64_t R_cap) {
     return R_cap < (1ull << 11) ? 0u : R_cap < (1ull << 14) ? 1u : R_cap < (1ull << 17) ? 2u : 3u;
 }
-static uint64_t tune_key(uint32_t L, uint32_t q_large, uint32_t r_class) {
-    return ((uint64_t)L << 8) | ((uint64_t)(q_large != 0) << 4) | r_class;
+// The kernel classes of the tuned shapes (pa_tune_entry.q_large): runs and
+// steps the quad kernel takes; those it does not, up to q = 128; q above 128.
+// The best shapes of the three differ.
+enum : uint32_t { TUNE_QUAD = 0, TUNE_LARGE = 1, TUNE_DWORD = 2 };
+static uint32_t tune_class(uint32_t q_large) { return q_large == TUNE_DWORD ? TUNE_DWORD : q_large != 0 ? TUNE_LARGE : TUNE_QUAD; }
+static uint32_t tune_class_of(uint32_t q) { return q > 128 ? TUNE_LARGE : q > 32 ? TUNE_DWORD : TUNE_QUAD; }
+static uint64_t tune_key(uint32_t L, uint32_t cls, uint32_t r_class) {
+    return ((uint64_t)L << 8) | ((uint64_t)cls << 4) | r_class;
+}
+// The entry a class uses: its own; without one the dword class uses that of the
+// quad class, if the dword kernel has its shape.
+static bool tune_find(pa_ctx *ctx, uint32_t L, uint32_t cls, uint32_t r_class, pa_tune_entry *e) {
+    std::lock_guard<std::mutex> lk(ctx->tune_mu);
+    auto it = ctx->tune.find(tune_key(L, cls, r_class));
+    if (it == ctx->tune.end() && cls == TUNE_DWORD) {
+        it = ctx->tune.find(tune_key(L, TUNE_QUAD, r_class));
+        if (it != ctx->tune.end() && pa::quad_only(L, it->second.lanes, it->second.waves_per_block)) it = ctx->tune.end();
+    }
+    if (it == ctx->tune.end()) return false;
+    *e = it->second;
+    return true;
+}
+// Installs an entry (tune_mu held).  One of the quad class is for every q up to
+// 128 until an entry of the dword class follows it.
+static void tune_install(pa_ctx *ctx, const pa_tune_entry &e) {
+    const uint32_t cls = tune_class(e.q_large);
+    if (cls == TUNE_QUAD) ctx->tune.erase(tune_key(e.L, TUNE_DWORD, e.r_class));
+    ctx->tune[tune_key(e.L, cls, e.r_class)] = e;
+    ++ctx->tune_gen;
 }
 
 static uint32_t ctx_lanes(const pa_ctx *c, uint32_t L) {
@@ -413,7 +440,10 @@ struct pa_run_state {
     int cur;             // pop buffer holding the current population
     uint64_t R_cur, R_prev;
     uint64_t r_dirty[2];  // extent of nonzero copy counts in each parity buffer
-    uint32_t G, wpb;     // sweep shape: lanes per replica, waves per workgroup
+    // sweep shapes: for the steps that the quad kernel takes, if it has the shape
+    // (G lanes per replica, wpb waves per workgroup), and for all others
+    uint32_t G, wpb;
+    pa::SweepShape dshape;
     bool free_shape;     // not fixed by a lane count set on the context or by tuning
     bool dword;          // loaded spins beyond the quad kernel's: it is not used
     double mbF0;
@@ -724,7 +754,7 @@ pa_status do_step(pa_run_state *r) {
             return st;
     } else {
         pa::SweepArgs a = sweep_args(r, i, pa::SWEEP_UPDATE, old_pop, anc, new_pop, p.desc.theta);
-        if ((st = timed_launch(r, PA_KERNEL_SWEEP, "sweep kernel", [&] { return pa::launch_sweep(a, r->stream); })))
+        if ((st = timed_launch(r, PA_KERNEL_SWEEP, "sweep kernel", [&] { return pa::launch_sweep(a, r->dshape, r->stream); })))
             return st;
     }
     r->cur = 1 - r->cur;
@@ -983,10 +1013,11 @@ pa_status pa_autotune(pa_ctx *ctx, uint32_t L, uint32_t q, void *d_ws, uint64_t 
     return PA_OK;
 }
 
-// The sweep shapes a tuned entry may take for lattice side L: every lane
-// count with a kernel for L, and for each the waves per workgroup that keep a
-// workgroup within 1024 threads (256 for the byte kernel) and the LDS.
-static std::vector<std::pair<uint32_t, uint32_t>> tune_candidates(uint32_t L, int device) {
+// The sweep shapes a tuned entry of a class may take for lattice side L: every
+// lane count with a kernel for L, and for each the waves per workgroup that keep
+// a workgroup within 1024 threads (256 for the byte kernel) and the LDS; for the
+// quad class also the shapes that only its kernel has.
+static std::vector<std::pair<uint32_t, uint32_t>> tune_candidates(uint32_t L, uint32_t cls, int device) {
     std::vector<std::pair<uint32_t, uint32_t>> out;
     if (pa::tiled_path(L)) return out;
     const uint32_t N = L * L;
@@ -996,7 +1027,7 @@ static std::vector<std::pair<uint32_t, uint32_t>> tune_candidates(uint32_t L, in
     };
     // shapes only the quad kernel has: workgroups of a multiple of four waves
     uint32_t ql[4];
-    const uint32_t nq = pa::quad_lanes(L, ql);
+    const uint32_t nq = cls == TUNE_QUAD ? pa::quad_lanes(L, ql) : 0u;
     for (uint32_t c = 0; c < nq; ++c)
         for (uint32_t w = 4; w <= 16; w += 4)
             if (pa::quad_only(L, ql[c], w) && pa::quad_max_nr(L, 2, false, ql[c], w)) out.push_back({ql[c], w});
@@ -1028,7 +1059,7 @@ static std::vector<std::pair<uint32_t, uint32_t>> tune_candidates(uint32_t L, in
 }
 
 static pa_status tune_check(pa_ctx *ctx, const pa_tune_entry *e) {
-    for (const auto &c : tune_candidates(e->L, ctx->device))
+    for (const auto &c : tune_candidates(e->L, tune_class(e->q_large), ctx->device))
         if (c.first == e->lanes && c.second == e->waves_per_block) return PA_OK;
     return fail(PA_ERR_INVALID, "not a sweep shape of this lattice side");
 }
@@ -1038,8 +1069,7 @@ pa_status pa_tune_set(pa_ctx *ctx, const pa_tune_entry *e) {
     pa_status st = tune_check(ctx, e);
     if (st) return st;
     std::lock_guard<std::mutex> lk(ctx->tune_mu);
-    ctx->tune[tune_key(e->L, e->q_large, e->r_class)] = *e;
-    ++ctx->tune_gen;
+    tune_install(ctx, *e);
     return PA_OK;
 }
 
@@ -1047,15 +1077,11 @@ pa_status pa_tune_get(pa_ctx *ctx, uint32_t L, uint32_t q, uint64_t R, pa_tune_e
     if (!ctx || !e) return fail(PA_ERR_INVALID, "null argument");
     pa_tune_entry t{};
     t.L = L;
-    t.q_large = q > 128 ? 1u : 0u;
+    t.q_large = tune_class_of(q);
     t.r_class = r_class_of(R);
     if (pa::tiled_path(L)) return fail(PA_ERR_INVALID, "the tiled path has no sweep shape");
-    pa::sweep_shape(L, ctx_lanes(ctx, L), &t.lanes, &t.waves_per_block);
-    if (ctx_lanes(ctx, L) == 0) {
-        std::lock_guard<std::mutex> lk(ctx->tune_mu);
-        auto it = ctx->tune.find(tune_key(t.L, t.q_large, t.r_class));
-        if (it != ctx->tune.end()) t = it->second;
-    }
+    (t.q_large == TUNE_QUAD ? pa::sweep_shape : pa::dword_shape)(L, ctx_lanes(ctx, L), &t.lanes, &t.waves_per_block);
+    if (ctx_lanes(ctx, L) == 0) (void)tune_find(ctx, L, t.q_large, t.r_class, &t);
     *e = t;
     return PA_OK;
 }
@@ -1063,7 +1089,7 @@ pa_status pa_tune_get(pa_ctx *ctx, uint32_t L, uint32_t q, uint64_t R, pa_tune_e
 pa_status pa_tune(pa_ctx *ctx, uint32_t L, uint32_t q, uint64_t R, void *d_ws, uint64_t ws_bytes, void *stream,
                   pa_tune_entry *best, pa_tune_entry *timed, uint32_t timed_cap, uint32_t *n_timed) {
     if (!ctx || !best) return fail(PA_ERR_INVALID, "null argument");
-    const auto cands = tune_candidates(L, ctx->device);
+    const auto cands = tune_candidates(L, tune_class_of(q), ctx->device);
     if (cands.empty()) return fail(PA_ERR_INVALID, "no sweep shapes for this lattice side");
     const double beta[3] = {0.0, 0.5, 1.0};
     pa_run_desc d{};
@@ -1076,7 +1102,7 @@ pa_status pa_tune(pa_ctx *ctx, uint32_t L, uint32_t q, uint64_t R, void *d_ws, u
     const int saved_prof = ctx->profiling;
     pa_tune_entry b{};
     b.L = L;
-    b.q_large = q > 128 ? 1u : 0u;
+    b.q_large = tune_class_of(q);
     b.r_class = r_class_of(R);
     b.attempts_per_ns = -1.0;
     uint32_t nt = 0;
@@ -1208,8 +1234,7 @@ pa_status pa_tune_load(pa_ctx *ctx, const char *path, uint32_t *n_loaded) {
     if (st) return st;
     {
         std::lock_guard<std::mutex> lk(ctx->tune_mu);
-        for (const auto &e : got) ctx->tune[tune_key(e.L, e.q_large, e.r_class)] = e;
-        ++ctx->tune_gen;
+        for (const auto &e : got) tune_install(ctx, e);
     }
     if (n_loaded) *n_loaded = (uint32_t)got.size();
     return PA_OK;
@@ -1300,34 +1325,40 @@ pa_status begin_run(pa_ctx *ctx, const pa_run_desc *desc, void *d_ws, uint64_t w
     r->broken = false;
     r->G = 0;
     r->wpb = 0;
+    r->dshape = {0, 0};
     r->dword = false;
     r->free_shape = !ctx->tune_try_G && ctx_lanes(ctx, p.desc.L) == 0;
     if (!p.tiled) {
         // a lane count set on the context, else the tuned shape of this
         // class, else the default
-        pa::sweep_shape(p.desc.L, ctx_lanes(ctx, p.desc.L), &r->G, &r->wpb);
-        uint32_t tG = 0, tw = 0;
-        if (ctx->tune_try_G) {
-            tG = ctx->tune_try_G;
-            tw = ctx->tune_try_wpb;
-        } else if (ctx_lanes(ctx, p.desc.L) == 0) {
-            std::lock_guard<std::mutex> lk(ctx->tune_mu);
-            auto it = ctx->tune.find(tune_key(p.desc.L, p.desc.q > 128, r_class_of(p.R_cap)));
-            if (it != ctx->tune.end()) {
-                tG = it->second.lanes;
-                tw = it->second.waves_per_block;
+        const uint32_t L = p.desc.L, q = p.desc.q, qc = p.mag ? q : 0u, lanes = ctx_lanes(ctx, L);
+        const size_t lds_max = pa::max_lds_per_block(ctx->device);
+        auto pick = [&](uint32_t cls) {
+            pa::SweepShape d;
+            (cls == TUNE_QUAD ? pa::sweep_shape : pa::dword_shape)(L, lanes, &d.lanes, &d.waves_per_block);
+            pa_tune_entry t{};
+            if (ctx->tune_try_G) {
+                if (cls == TUNE_QUAD || !pa::quad_only(L, ctx->tune_try_G, ctx->tune_try_wpb)) {
+                    t.lanes = ctx->tune_try_G;
+                    t.waves_per_block = ctx->tune_try_wpb;
+                }
+            } else if (lanes == 0) {
+                (void)tune_find(ctx, L, cls, r_class_of(p.R_cap), &t);
             }
+            if (t.lanes && (cls == TUNE_QUAD ? pa::shape_lds_bytes(L, q, t.lanes, t.waves_per_block, qc)
+                                             : pa::sweep_lds_bytes(p.N, t.lanes, t.waves_per_block, qc)) <= lds_max)
+                d = {t.lanes, t.waves_per_block};
+            return d;
+        };
+        r->dshape = pick(q > 128 ? TUNE_LARGE : TUNE_DWORD);
+        const pa::SweepShape s = q <= 32 ? pick(TUNE_QUAD) : r->dshape;
+        r->G = s.lanes;
+        r->wpb = s.waves_per_block;
+        if (pa::shape_lds_bytes(L, q, r->G, r->wpb, qc) > lds_max ||
+            pa::sweep_lds_bytes(p.N, r->dshape.lanes, r->dshape.waves_per_block, qc) > lds_max) {
+            delete r;
+            return fail(PA_ERR_UNSUPPORTED, "lattice does not fit the LDS of one workgroup on this device");
         }
-        if (tG && pa::shape_lds_bytes(p.desc.L, p.desc.q, tG, tw, p.mag ? p.desc.q : 0u) <=
-                      pa::max_lds_per_block(ctx->device)) {
-            r->G = tG;
-            r->wpb = tw;
-        }
-    }
-    if (!p.tiled && pa::shape_lds_bytes(p.desc.L, p.desc.q, r->G, r->wpb, p.mag ? p.desc.q : 0u) >
-                        pa::max_lds_per_block(ctx->device)) {
-        delete r;
-        return fail(PA_ERR_UNSUPPORTED, "lattice does not fit the LDS of one workgroup on this device");
     }
     if ((st = hip_check(r, hipSetDevice(ctx->device), "hipSetDevice"))) { delete r; return st; }
     // ln Z at beta_0: N ln q (Z = q^N at beta = 0, Sec. 6) or, for ground
@@ -1359,7 +1390,7 @@ pa_status begin_run(pa_ctx *ctx, const pa_run_desc *desc, void *d_ws, uint64_t w
     pa::SweepArgs a = sweep_args(r, 0, mode, nullptr, nullptr, r->at<uint8_t>(p.off_pop[0]), 0);
     const pa::TiledArgs ta = tiled_args(r, 0, nullptr, nullptr, r->at<uint8_t>(p.off_pop[0]));
     auto init = [&]() -> hipError_t {
-        if (!p.tiled) return pa::launch_sweep(a, s);
+        if (!p.tiled) return pa::launch_sweep(a, r->dshape, s);
         const hipError_t e = pa::launch_tiled_init(ta, s);
         return e != hipSuccess ? e : pa::launch_tiled_measure(ta, s);
     };
@@ -1477,7 +1508,7 @@ pa_status pa_run_load(pa_run_state *r, uint32_t step, uint64_t R_cur, const uint
     } else {
         pa::SweepArgs a = sweep_args(r, step, pa::SWEEP_UPDATE, r->at<uint8_t>(p.off_pop[idle]), nullptr,
                                      r->at<uint8_t>(p.off_pop[r->cur]), 0);
-        if ((st = hip_check(r, pa::launch_sweep(a, s), "load kernel"))) return st;
+        if ((st = hip_check(r, pa::launch_sweep(a, r->dshape, s), "load kernel"))) return st;
     }
     if ((st = launch_post_for(r, step))) return st;
     return hip_check(r, hipStreamSynchronize(s), "sync");
@@ -1821,11 +1852,11 @@ StepLaunch build_step(const std::vector<pa_run_state *> &active, std::vector<uin
     std::vector<uint32_t> sstart, mstart;
     std::vector<pa::SlotmapArgs> sm;
     std::vector<pa::PostArgs> po;
-    struct SW { pa::SweepLaunch l; uint32_t threads; pa::SweepArgs a; const pa_run_state *r; };
+    struct SW { pa::SweepLaunch l; uint32_t threads; pa::SweepArgs a; const pa_run_state *r; pa::SweepShape dshape; };
     std::vector<SW> sw;
     uint32_t sblocks = 0, mblocks = 0;
     const pa_run_state *run = nullptr;
-    auto add_sweep = [&](const pa::SweepArgs &a) { sw.push_back({pa::SweepLaunch{}, 0u, a, run}); };
+    auto add_sweep = [&](const pa::SweepArgs &a) { sw.push_back({pa::SweepLaunch{}, 0u, a, run, run->dshape}); };
     for (pa_run_state *r : active) {
         const Plan &p = r->plan;
         run = r;
@@ -1893,31 +1924,34 @@ StepLaunch build_step(const std::vector<pa_run_state *> &active, std::vector<uin
     // Several small runs of one side fill the GPU like one large run: their
     // shape is the tuned one of the class of their replicas together (20 runs
     // of 8x8, R = 1000: sweeps of 18.1 us with 8 lanes, 19.1 with 16).
-    struct Side { uint64_t key, replicas; bool found; pa_tune_entry t; };
+    struct Side { uint32_t L, cls; uint64_t replicas; bool found, dfound; pa_tune_entry t, d; };
     std::vector<Side> sides;
     auto side_of = [&](const pa::SweepArgs &a) -> Side & {
-        const uint64_t key = tune_key(a.L, a.q > 128, 0u);
-        for (Side &d : sides) if (d.key == key) return d;
-        sides.push_back({key, 0u, false, {}});
+        const uint32_t cls = a.q > 128 ? TUNE_LARGE : pa::quad_step(a) ? TUNE_QUAD : TUNE_DWORD;
+        for (Side &d : sides) if (d.L == a.L && d.cls == cls) return d;
+        sides.push_back({a.L, cls, 0u, false, false, {}, {}});
         return sides.back();
     };
     for (const SW &e : sw)
         if (e.r->free_shape) side_of(e.a).replicas += e.a.R_new;
     for (Side &d : sides) {
         pa_ctx *ctx = active[0]->ctx;
-        std::lock_guard<std::mutex> lk(ctx->tune_mu);
-        const auto it = ctx->tune.find(d.key | r_class_of(d.replicas));
-        if ((d.found = it != ctx->tune.end())) d.t = it->second;
+        const uint32_t rc = r_class_of(d.replicas);
+        d.found = d.cls == TUNE_QUAD && tune_find(ctx, d.L, TUNE_QUAD, rc, &d.t);
+        d.dfound = tune_find(ctx, d.L, d.cls == TUNE_LARGE ? TUNE_LARGE : TUNE_DWORD, rc, &d.d);
     }
     const size_t lds_cap = sides.empty() ? 0 : pa::max_lds_per_block(active[0]->ctx->device);
     for (SW &e : sw) {
         if (!e.r->free_shape) continue;
         const Side &d = side_of(e.a);
-        if (!d.found || r_class_of(d.replicas) <= r_class_of(e.r->plan.R_cap) ||
-            pa::shape_lds_bytes(e.a.L, e.a.q, d.t.lanes, d.t.waves_per_block, e.a.Mt_out ? e.a.q : 0u) > lds_cap)
-            continue;
-        e.a.G = d.t.lanes;
-        e.a.waves_per_block = (uint16_t)d.t.waves_per_block;
+        if (r_class_of(d.replicas) <= r_class_of(e.r->plan.R_cap)) continue;
+        const uint32_t qc = e.a.Mt_out ? e.a.q : 0u;
+        if (d.found && pa::shape_lds_bytes(e.a.L, e.a.q, d.t.lanes, d.t.waves_per_block, qc) <= lds_cap) {
+            e.a.G = d.t.lanes;
+            e.a.waves_per_block = (uint16_t)d.t.waves_per_block;
+        }
+        if (d.dfound && pa::sweep_lds_bytes(e.a.N, d.d.lanes, d.d.waves_per_block, qc) <= lds_cap)
+            e.dshape = {d.d.lanes, d.d.waves_per_block};
     }
     // the kernels, from all the replicas that runs of one shape bring
     auto shape_key = [](const pa::SweepArgs &a) {
@@ -1926,7 +1960,7 @@ StepLaunch build_step(const std::vector<pa_run_state *> &active, std::vector<uin
     KeySums replicas;
     for (const SW &e : sw) replicas[shape_key(e.a)] += e.a.R_new;
     std::vector<uint32_t> nr;
-    for (SW &e : sw) nr.push_back(pa::settle_sweep(e.a, replicas[shape_key(e.a)]));
+    for (SW &e : sw) nr.push_back(pa::settle_sweep(e.a, e.dshape, replicas[shape_key(e.a)]));
     // several replicas per lane in the first runs of a launch, one in the last
     replicas.v.clear();
     for (size_t k = 0; k < sw.size(); ++k)
@@ -2136,10 +2170,10 @@ constexpr uint64_t kTeamTimeoutTicks = 1000000000ull;   // 10 s of the 100 MHz c
 uint32_t team_class(const pa_run_state *r) {
     const Plan &p = r->plan;
     if (p.tiled || p.R_cap > kTeamRMax || r->step + 1 >= p.desc.K) return 0;
-    if (pa::quad_only(p.desc.L, r->G, r->wpb) || pa::team_threads() % (64u * r->wpb) != 0) return 0;
+    if (pa::quad_only(p.desc.L, r->G, r->wpb) || pa::team_threads() % (64u * r->dshape.waves_per_block) != 0) return 0;
     for (uint32_t i = r->step + 1; i < p.desc.K; ++i)
         if (p.T[(size_t)i * 4 + 3] == 0) return 0;
-    const uint32_t cls = pa::sweep_class(p.desc.L, p.desc.q, false, r->G);
+    const uint32_t cls = pa::sweep_class(p.desc.L, p.desc.q, false, r->dshape.lanes);
     return pa::team_kernel(cls) ? cls : 0u;
 }
 
@@ -2185,6 +2219,8 @@ void team_records(pa_run_state *r, std::vector<pa::TeamStep> &recs, pa::TeamRun 
         r->R_cur = R_new;
         t.w = sweep_args(r, i, pa::SWEEP_UPDATE, r->at<uint8_t>(p.off_pop[r->cur]), nullptr,
                          r->at<uint8_t>(p.off_pop[1 - r->cur]), p.desc.theta);
+        t.w.G = r->dshape.lanes;
+        t.w.waves_per_block = (uint16_t)r->dshape.waves_per_block;
         t.w.E_out = cur.E;
         t.w.Mt_out = cur.Mt;
         t.w.H_out = cur.H;
@@ -2202,8 +2238,9 @@ pa_status run_team_launch(pa_ctx *ctx, uint32_t cls, std::vector<pa_run_state *>
     pa_status st;
     // shape of the class: sweep groups of 64 * waves_per_block threads
     const pa_run_state *r0 = group[0];
-    const uint32_t BS = 64u * r0->wpb, SUB = pa::team_threads() / BS;
-    const uint32_t rpb = (uint32_t)pa::replicas_per_block(r0->G, r0->wpb);
+    const pa::SweepShape d = r0->dshape;
+    const uint32_t BS = 64u * d.waves_per_block, SUB = pa::team_threads() / BS;
+    const uint32_t rpb = (uint32_t)pa::replicas_per_block(d.lanes, d.waves_per_block);
     size_t sub_lds = 0;
     uint64_t r_max = 1;
     uint32_t n_max = 1;
@@ -2212,7 +2249,7 @@ pa_status run_team_launch(pa_ctx *ctx, uint32_t cls, std::vector<pa_run_state *>
     for (uint32_t k = 0; k < n; ++k) {
         const pa_run_state *r = group[k];
         const Plan &p = r->plan;
-        sub_lds = std::max(sub_lds, (pa::sweep_lds_bytes(p.N, r->G, r->wpb, p.mag ? p.desc.q : 0u) + 15) & ~size_t(15));
+        sub_lds = std::max(sub_lds, (pa::sweep_lds_bytes(p.N, d.lanes, d.waves_per_block, p.mag ? p.desc.q : 0u) + 15) & ~size_t(15));
         r_max = std::max(r_max, p.R_cap);
         n_max = std::max(n_max, p.N);
         // sweep workgroups beyond one block each would only repeat the
@@ -2428,7 +2465,7 @@ extern "C" pa_status pa_run_batch(pa_ctx *ctx, const pa_run_desc *descs, uint32_
         if ((st = hip_check(nullptr, hipStreamSynchronize(s), "sync"))) return cleanup(st);
         std::map<std::pair<uint32_t, uint32_t>, std::vector<uint32_t>> by_class;   // (class, waves per group)
         for (uint32_t r = 0; r < n; ++r)
-            if (const uint32_t cls = team_class(runs[r])) by_class[{cls, runs[r]->wpb}].push_back(r);
+            if (const uint32_t cls = team_class(runs[r])) by_class[{cls, runs[r]->dshape.waves_per_block}].push_back(r);
         for (auto &kv : by_class) {
             // a group too large for one launch is split in halves (launched one
             // after the other); a single run that does not fit goes segmented

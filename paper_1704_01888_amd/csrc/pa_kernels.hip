@@ -2323,49 +2323,44 @@ bool quad_only(uint32_t L, uint32_t G, uint32_t waves_per_block) {
 size_t shape_lds_bytes(uint32_t L, uint32_t q, uint32_t G, uint32_t waves_per_block, uint32_t q_counters) {
     const uint32_t nr = quad_max_nr(L, q, false, G, waves_per_block);
     if (nr) return quad_lds_bytes(L, G, waves_per_block, nr, q, q_counters);
-    if (quad_only(L, G, waves_per_block)) dword_shape(L, 0, &G, &waves_per_block);
     return sweep_lds_bytes(L * L, G, waves_per_block, q_counters);
 }
 
-uint32_t sweep_max_nr(const SweepArgs &a) {
-    return a.dword ? 0u : quad_max_nr(a.L, a.q, a.T[3] == 0, a.G, a.waves_per_block);
-}
+bool quad_step(const SweepArgs &a) { return !a.dword && a.q <= 32 && a.T[3] != 0; }
 
 // Settles the kernel of a sweep in a launch that holds `replicas` of its class
 // in all and returns its largest number of replicas per lane (0: not the quad
-// kernel).
-//   - A step the quad kernel does not take, with a shape only it has: the
-//     dword kernel's default shape.
-//   - Sides with lane choices: such a shape needs a launch of QUAD_MIN_WAVES,
-//     one round of the two 12-wave workgroups a compute unit holds; below it
-//     the side's default shape is used (theta = 10, quads / default, attempts
-//     per ns: 24x24 766 / 887 with 4000 waves and 1071 / 956 with 8000; 48x48
-//     767 / 865 and 1062 / 984; 96x96 767 / 891 and 1070 / 973).
+// kernel).  `dword`: the shape tuned for the dword kernel.
+//   - A step the quad kernel does not take: that shape (the best ones of the
+//     two kernels differ: 128x128, q = 40, 1024 lanes 1216 attempts/ns, 512
+//     lanes 1281).
+//   - Sides with lane choices: a shape that only the quad kernel has needs a
+//     launch of QUAD_MIN_WAVES, one round of the two 12-wave workgroups a
+//     compute unit holds; below it the dword shape is used (theta = 10, quads /
+//     default shape, attempts per ns: 24x24 766 / 887 with 4000 waves and 1071 /
+//     956 with 8000; 48x48 767 / 865 and 1062 / 984; 96x96 767 / 891 and 1070 /
+//     973).
 //   - Other sides: workgroups of fewer waves until there are two per compute
 //     unit.
 constexpr uint64_t QUAD_MIN_WAVES = 6144, QUAD_MIN_BLOCKS = 512;
-static void default_shape(SweepArgs &a, void (*shape)(uint32_t, uint32_t, uint32_t *, uint32_t *)) {
-    uint32_t w;
-    shape(a.L, 0, &a.G, &w);
-    a.waves_per_block = (uint16_t)w;
-}
-uint32_t settle_sweep(SweepArgs &a, uint64_t replicas) {
-    uint32_t max_nr = sweep_max_nr(a);
-    if (max_nr == 0) {
-        if (quad_only(a.L, a.G, a.waves_per_block)) default_shape(a, dword_shape);
+uint32_t settle_sweep(SweepArgs &a, SweepShape dword, uint64_t replicas) {
+    auto max_nr = [&] { return quad_max_nr(a.L, a.q, false, a.G, a.waves_per_block); };
+    auto take_dword = [&] {
+        a.G = dword.lanes;
+        a.waves_per_block = (uint16_t)dword.waves_per_block;
+    };
+    if (!quad_step(a)) {
+        take_dword();
         return 0;
     }
-    if (quad_any_side(a.L)) {
+    if (max_nr() != 0 && quad_any_side(a.L)) {
         const uint32_t least = (a.G + 63u) / 64u;
         while (a.waves_per_block > least && replicas < QUAD_MIN_BLOCKS * (64u * a.waves_per_block / a.G))
             a.waves_per_block = (uint16_t)(a.waves_per_block >= least + 4u ? a.waves_per_block - 4u : least);
-        return max_nr;
+    } else if (quad_only(a.L, a.G, a.waves_per_block) && replicas * a.G / 64u < QUAD_MIN_WAVES) {
+        take_dword();
     }
-    if (quad_only(a.L, a.G, a.waves_per_block) && replicas * a.G / 64u < QUAD_MIN_WAVES) {
-        default_shape(a, sweep_shape);
-        max_nr = sweep_max_nr(a);
-    }
-    return max_nr;
+    return max_nr();
 }
 
 // (see quad_shape; all of them below two shares, where the long waves would be
@@ -2397,9 +2392,9 @@ SweepLaunch sweep_launch(const SweepArgs &a, uint32_t nr) {
     return l;
 }
 
-hipError_t launch_sweep(const SweepArgs &args, hipStream_t s) {
+hipError_t launch_sweep(const SweepArgs &args, SweepShape dword, hipStream_t s) {
     SweepArgs a = args;
-    uint32_t nr = settle_sweep(a, a.R_new);
+    uint32_t nr = settle_sweep(a, dword, a.R_new);
     if (nr > 1) {
         const uint64_t singles = quad_singles(a, nr, a.R_new);
         if (a.R_new > singles)

@@ -177,7 +177,7 @@ def test_shapes_that_only_the_quad_kernel_has_go_segmented():
         shapes = {32: [(128, w) for w in (4, 8, 12, 16)], 64: [(512, 16)]}
         for L, R in ((32, 300), (64, 130)):
             cases = [dict(L=L, q=q, R=R + q, beta=linear_betas(1.2, 6), theta=2, seed=80 + q, resample=1)
-                     for q in (10, 20, 40)]
+                     for q in (10, 20, 32)]
             descs = [pa.Desc(outputs=ALL, **k) for k in cases]
             want = [oracle.run(oracle.Desc(**k), hist=True, final=True, digest=True, magnetisation=True) for k in cases]
             for G, w in shapes[L]:

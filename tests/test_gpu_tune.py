@@ -119,3 +119,92 @@ def test_one_class_with_two_tuned_workgroup_sizes_in_a_batch(ctx, mode):
         ctx.set_batch_mode(pa.BATCH_SEGMENTED)
     for d, g in zip(descs, got):
         _same(g, pa.pa_run(ctx, d))
+
+
+@pytest.fixture()
+def plain():
+    c = pa.Context(0, tune_cache=False)
+    yield c
+    c.close()
+
+
+def _get(c, L, q, R):
+    e = c.tune_get(L, q, R)
+    return e["lanes"], e["waves_per_block"]
+
+
+def test_the_kernel_classes_have_entries_of_their_own(plain):
+    c = plain
+    # without a dword entry: the quad class's shape, or the default where only
+    # the quad kernel has it; q above 128 is apart
+    c.tune_set(24, 0, 2, 48, 9)
+    assert _get(c, 24, 40, 50000) == _get(c, 24, 8, 50000) == (48, 9)
+    c.tune_set(24, 0, 2, 24, 12)
+    assert _get(c, 24, 8, 50000) == (24, 12) and _get(c, 24, 32, 50000) == (24, 12)
+    assert _get(c, 24, 33, 50000) == _get(c, 24, 128, 50000) == _get(c, 24, 129, 50000) == (48, 3)
+    c.tune_set(24, 2, 2, 48, 12)
+    assert _get(c, 24, 8, 50000) == (24, 12)
+    assert _get(c, 24, 33, 50000) == _get(c, 24, 128, 50000) == (48, 12)
+    assert _get(c, 24, 129, 50000) == (48, 3)
+    # a later entry for every q up to 128 takes its place
+    c.tune_set(24, 0, 2, 48, 6)
+    assert _get(c, 24, 40, 50000) == _get(c, 24, 8, 50000) == (48, 6)
+    # a side without lane choices: the dword kernel's shape above q = 32
+    assert _get(c, 50, 8, 3000) != _get(c, 50, 40, 3000) == (64, 4)
+
+
+@pytest.mark.parametrize("q_large", [1, 2])
+@pytest.mark.parametrize("L,lanes,waves", [(24, 24, 12), (32, 128, 8), (64, 512, 16), (96, 384, 12)])
+def test_other_classes_refuse_the_quad_kernels_own_shapes(plain, L, lanes, waves, q_large):
+    with pytest.raises(pa.PAError) as e:
+        plain.tune_set(L, q_large, 1, lanes, waves)
+    assert e.value.status == pa.PA_ERR_INVALID
+    plain.tune_set(L, 0, 1, lanes, waves)
+
+
+def test_the_shipped_shapes_of_the_dword_kernel(ctx):
+    """Where the two kernels' best shapes differ, each has its own."""
+    c = pa.Context(0)
+    try:
+        assert _get(c, 24, 40, 8000) == _get(c, 24, 40, 50000) == (48, 12)
+        assert _get(c, 128, 40, 50000) == (512, 8) and _get(c, 128, 10, 50000) == (1024, 16)
+        assert _get(c, 32, 40, 8000) == (256, 4)
+    finally:
+        c.close()
+
+
+def test_tuning_above_32_states_leaves_the_quad_class_alone(plain, tmp_path):
+    plain.tune_set(32, 0, 1, 128, 4)
+    e = plain.tune(32, 40, 4000)
+    assert e["q_large"] == 2 and all((t["lanes"], t["waves_per_block"]) in ((256, 4), (128, 2)) for t in e["timed"])
+    assert _get(plain, 32, 40, 4000) == (e["lanes"], e["waves_per_block"])
+    assert _get(plain, 32, 8, 4000) == (128, 4)
+    path = tmp_path / "classes.jsonl"
+    plain.tune_save(path)
+    other = pa.Context(0, tune_cache=False)
+    try:
+        assert other.tune_load(path) == 2
+        assert _get(other, 32, 40, 4000) == (e["lanes"], e["waves_per_block"])
+        assert _get(other, 32, 8, 4000) == (128, 4)
+    finally:
+        other.close()
+
+
+def test_steps_of_both_kernels_with_an_entry_each(plain):
+    """64-bit thresholds in the middle of a run, q on both sides of 32, alone,
+    in a batch (the shape of all replicas together) and in team launches."""
+    for r_class in range(4):
+        for L, quad, dword in ((24, (24, 12), (48, 9)), (32, (128, 8), (256, 4)), (64, (512, 8), (1024, 16))):
+            plain.tune_set(L, 0, r_class, *quad)
+            plain.tune_set(L, 2, r_class, *dword)
+    runs = [dict(L=L, q=q, R=R, beta=linear_betas(b, 4), theta=2, seed=500 + q + L, resample=1)
+            for L, R in ((24, 1500), (32, 900), (64, 300)) for q, b in ((10, 1.2), (20, 6.0), (40, 1.2))]
+    want = [oracle.run(oracle.Desc(**r), hist=True, final=True, digest=True) for r in runs]
+    descs = [pa.Desc(outputs=pa.OUT_HIST | pa.OUT_FINAL | pa.OUT_DIGEST, **r) for r in runs]
+    for d, w in zip(descs, want):
+        print(f"\nL={d.L} q={d.q} R={d.R}", flush=True)
+        _same(pa.pa_run(plain, d), w)
+    for mode in (pa.BATCH_SEGMENTED, pa.BATCH_TEAM):
+        plain.set_batch_mode(mode)
+        for g, w in zip(pa.pa_run_batch(plain, descs), want):
+            _same(g, w)

@@ -217,7 +217,8 @@ pa_status pa_autotune(pa_ctx *ctx, uint32_t L, uint32_t q, void *d_ws, uint64_t 
  * the tiled path (L > 256) have no shape.
  * pa_tune: times every shape of L (each lane count with a kernel for L; for
  *   each, the waves per workgroup that fit 1024 threads, 256 for L = 2 mod 4,
- *   and the LDS) on a synthetic run of R replicas (K = 3, theta = 10) in the
+ *   and the LDS; for q up to 32 the four-site kernel's, but for those that
+ *   R replicas are too few for) on a synthetic run of R replicas (K = 3, theta = 10) in the
  *   caller's workspace (at least pa_plan's size for that run), keeps the
  *   fastest as the entry of (L, q, R)'s class (q_large 0 for q up to 32, 2 up
  *   to 128, 1 above) and returns it with its rate;

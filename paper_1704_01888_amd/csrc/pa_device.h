@@ -291,6 +291,9 @@ bool quad_step(const SweepArgs &a);
 uint32_t quad_max_nr(uint32_t L, uint32_t q, bool t64, uint32_t G, uint32_t waves_per_block);
 uint32_t quad_lanes(uint32_t L, uint32_t *out);
 bool quad_only(uint32_t L, uint32_t G, uint32_t waves_per_block);
+// Whether a launch of `replicas` has enough waves for a shape that only the
+// quad kernel has (others: true).
+bool quad_fills(uint32_t L, uint32_t G, uint32_t waves_per_block, uint64_t replicas);
 // LDS of a workgroup of a shape, whichever kernel takes it.
 size_t shape_lds_bytes(uint32_t L, uint32_t q, uint32_t G, uint32_t waves_per_block, uint32_t q_counters);
 struct SweepLaunch { uint32_t cls, blocks; uint64_t per_block; size_t lds; };

@@ -1107,6 +1107,7 @@ pa_status pa_tune(pa_ctx *ctx, uint32_t L, uint32_t q, uint64_t R, void *d_ws, u
     b.attempts_per_ns = -1.0;
     uint32_t nt = 0;
     for (const auto &c : cands) {
+        if (!pa::quad_fills(L, c.first, c.second, R)) continue;   // its runs would take another shape
         ctx->tune_try_G = c.first;
         ctx->tune_try_wpb = c.second;
         pa_result res{};

@@ -2343,6 +2343,9 @@ bool quad_step(const SweepArgs &a) { return !a.dword && a.q <= 32 && a.T[3] != 0
 //   - Other sides: workgroups of fewer waves until there are two per compute
 //     unit.
 constexpr uint64_t QUAD_MIN_WAVES = 6144, QUAD_MIN_BLOCKS = 512;
+bool quad_fills(uint32_t L, uint32_t G, uint32_t waves_per_block, uint64_t replicas) {
+    return quad_any_side(L) || !quad_only(L, G, waves_per_block) || replicas * G / 64u >= QUAD_MIN_WAVES;
+}
 uint32_t settle_sweep(SweepArgs &a, SweepShape dword, uint64_t replicas) {
     auto max_nr = [&] { return quad_max_nr(a.L, a.q, false, a.G, a.waves_per_block); };
     auto take_dword = [&] {
@@ -2357,7 +2360,7 @@ uint32_t settle_sweep(SweepArgs &a, SweepShape dword, uint64_t replicas) {
         const uint32_t least = (a.G + 63u) / 64u;
         while (a.waves_per_block > least && replicas < QUAD_MIN_BLOCKS * (64u * a.waves_per_block / a.G))
             a.waves_per_block = (uint16_t)(a.waves_per_block >= least + 4u ? a.waves_per_block - 4u : least);
-    } else if (quad_only(a.L, a.G, a.waves_per_block) && replicas * a.G / 64u < QUAD_MIN_WAVES) {
+    } else if (!quad_fills(a.L, a.G, a.waves_per_block, replicas)) {
         take_dword();
     }
     return max_nr();

@@ -208,3 +208,18 @@ def test_steps_of_both_kernels_with_an_entry_each(plain):
         plain.set_batch_mode(mode)
         for g, w in zip(pa.pa_run_batch(plain, descs), want):
             _same(g, w)
+
+
+def test_shapes_whose_launch_the_population_does_not_fill_are_not_timed(plain):
+    """Below one round of the 12-wave workgroups such a shape's runs take the
+    dword shape, whose rate must not be filed under it; at 24x24 that is every
+    population below 2^14."""
+    for L, R, lanes, timed in ((24, 8000, 24, False), (24, 17000, 24, True), (48, 2048, 96, False), (48, 5000, 96, True),
+                               (96, 1000, 384, False)):
+        e = plain.tune(L, 10, R)
+        assert ((lanes, 12) in {(t["lanes"], t["waves_per_block"]) for t in e["timed"]}) is timed, (L, R)
+    c = pa.Context(0)
+    try:
+        assert _get(c, 24, 10, 8000) == (48, 12) and _get(c, 24, 10, 50000) == (24, 12)
+    finally:
+        c.close()

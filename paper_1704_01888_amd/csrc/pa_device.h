@@ -196,6 +196,8 @@ hipError_t launch_post(const PostArgs &a, uint32_t *scratch, uint64_t scratch_wo
 hipError_t launch_resample(const SampleArgs &a, const SlotmapArgs &m, uint64_t *scratch, uint64_t scratch_words,
                            hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t s);
+// *flag = whether any of the n bytes at p (16-byte aligned) is q or more, q <= 128
+hipError_t launch_spins_beyond(const uint8_t *p, uint64_t n, uint32_t q, uint32_t *flag, hipStream_t s);
 
 // One launch of many small fills and copies (a batch's start: zeroed
 // histograms, counts and sums, weight tables; its end: the per-step result

@@ -446,6 +446,7 @@ struct pa_run_state {
     pa::SweepShape dshape;
     bool free_shape;     // not fixed by a lane count set on the context or by tuning
     bool dword;          // loaded spins beyond the quad kernel's: it is not used
+    uint32_t beyond;     // (read back from the device by pa_run_load)
     double mbF0;
     uint32_t first_step;  // step of the initial or loaded population
     uint64_t R_first;
@@ -1328,6 +1329,7 @@ pa_status begin_run(pa_ctx *ctx, const pa_run_desc *desc, void *d_ws, uint64_t w
     r->wpb = 0;
     r->dshape = {0, 0};
     r->dword = false;
+    r->beyond = 0;
     r->free_shape = !ctx->tune_try_G && ctx_lanes(ctx, p.desc.L) == 0;
     if (!p.tiled) {
         // a lane count set on the context, else the tuned shape of this
@@ -1475,10 +1477,9 @@ pa_status pa_run_load(pa_run_state *r, uint32_t step, uint64_t R_cur, const uint
     pa_status st;
     hipStream_t s = r->stream;
     // the quad kernel compares spins of five bits; a population with others
-    // (states beyond q) keeps the dword kernel
-    uint8_t top = 0;
-    for (size_t i = 0, n = (size_t)R_cur * p.N; i < n; ++i) top = std::max(top, spins[i]);
-    r->dword = top >= p.desc.q;
+    // (states beyond q) keeps the dword kernel, which also takes this call's sweep
+    r->dword = true;
+    r->beyond = 1;
     r->step = step;
     r->R_cur = R_cur;
     r->R_prev = R_cur;
@@ -1497,6 +1498,13 @@ pa_status pa_run_load(pa_run_state *r, uint32_t step, uint64_t R_cur, const uint
     if ((st = hip_check(r, hipMemcpyAsync(r->ws + p.off_pop[idle], spins, (size_t)R_cur * p.N,
                                           hipMemcpyHostToDevice, s), "upload spins")))
         return st;
+    if (p.desc.q <= 32) {
+        uint32_t *flag = r->at<uint32_t>(p.tiled ? p.off_pop_x : p.off_E2);   // (idle between steps)
+        if ((st = hip_check(r, pa::launch_spins_beyond(r->ws + p.off_pop[idle], (uint64_t)R_cur * p.N, p.desc.q, flag, s),
+                            "look at spins")) ||
+            (st = hip_check(r, hipMemcpyAsync(&r->beyond, flag, 4, hipMemcpyDeviceToHost, s), "read")))
+            return st;
+    }
     r->mbF0 = minus_beta_F;
     if ((st = hip_check(r, hipMemcpyAsync(r->at<double>(p.off_mbF) + step, &r->mbF0, 8,
                                           hipMemcpyHostToDevice, s), "upload")))
@@ -1511,8 +1519,9 @@ pa_status pa_run_load(pa_run_state *r, uint32_t step, uint64_t R_cur, const uint
                                      r->at<uint8_t>(p.off_pop[r->cur]), 0);
         if ((st = hip_check(r, pa::launch_sweep(a, r->dshape, s), "load kernel"))) return st;
     }
-    if ((st = launch_post_for(r, step))) return st;
-    return hip_check(r, hipStreamSynchronize(s), "sync");
+    if ((st = launch_post_for(r, step)) || (st = hip_check(r, hipStreamSynchronize(s), "sync"))) return st;
+    r->dword = r->beyond != 0;
+    return PA_OK;
 }
 
 pa_status pa_run_read_slots(pa_run_state *r, int previous, const uint32_t *slots, uint32_t n,

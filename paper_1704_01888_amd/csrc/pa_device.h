@@ -187,8 +187,9 @@ hipError_t launch_tiled_finalize(const TiledArgs &a, hipStream_t s);
 
 // A sweep shape: lanes per replica, waves per workgroup.
 struct SweepShape { uint32_t lanes, waves_per_block; };
-// (dword: the run's shape where the quad kernel does not take the step)
-hipError_t launch_sweep(const SweepArgs &a, SweepShape dword, hipStream_t s);
+// (dword: the run's shape where the quad kernel does not take the step; cus: the
+// device's compute units)
+hipError_t launch_sweep(const SweepArgs &a, SweepShape dword, uint32_t cus, hipStream_t s);
 // scratch (16-byte aligned, for the launch alone): `scratch_words` words, for
 // the block histograms / sums of large populations
 hipError_t launch_post(const PostArgs &a, uint32_t *scratch, uint64_t scratch_words, hipStream_t s);
@@ -295,13 +296,13 @@ uint32_t quad_lanes(uint32_t L, uint32_t *out);
 bool quad_only(uint32_t L, uint32_t G, uint32_t waves_per_block);
 // Whether a launch of `replicas` has enough waves for a shape that only the
 // quad kernel has (others: true).
-bool quad_fills(uint32_t L, uint32_t G, uint32_t waves_per_block, uint64_t replicas);
+bool quad_fills(uint32_t L, uint32_t G, uint32_t waves_per_block, uint64_t replicas, uint32_t cus);
 // LDS of a workgroup of a shape, whichever kernel takes it.
 size_t shape_lds_bytes(uint32_t L, uint32_t q, uint32_t G, uint32_t waves_per_block, uint32_t q_counters);
 struct SweepLaunch { uint32_t cls, blocks; uint64_t per_block; size_t lds; };
-uint32_t settle_sweep(SweepArgs &a, SweepShape dword, uint64_t replicas);
+uint32_t settle_sweep(SweepArgs &a, SweepShape dword, uint64_t replicas, uint32_t cus);
 // Of the `replicas` of a quad launch, those to be held one per lane (the last).
-uint64_t quad_singles(const SweepArgs &a, uint32_t nr, uint64_t replicas);
+uint64_t quad_singles(const SweepArgs &a, uint32_t nr, uint64_t replicas, uint32_t cus);
 SweepLaunch sweep_launch(const SweepArgs &a, uint32_t nr);
 // index of L in the table of lattices with lane choices (-1: none), and its size
 int lane_choice_index(uint32_t L);

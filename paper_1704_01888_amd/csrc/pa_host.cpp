@@ -345,6 +345,7 @@ struct GraphCache {
 
 struct pa_ctx {
     int device;
+    uint32_t cus;        // the device's compute units
     int profiling;
     uint32_t lanes[pa::LANE_CHOICE_COUNT];   // chosen lanes per replica per lattice with choices (0 = default)
     // The serving loop, shared with the pa_serve_* calls in flight: a call
@@ -755,7 +756,7 @@ pa_status do_step(pa_run_state *r) {
             return st;
     } else {
         pa::SweepArgs a = sweep_args(r, i, pa::SWEEP_UPDATE, old_pop, anc, new_pop, p.desc.theta);
-        if ((st = timed_launch(r, PA_KERNEL_SWEEP, "sweep kernel", [&] { return pa::launch_sweep(a, r->dshape, r->stream); })))
+        if ((st = timed_launch(r, PA_KERNEL_SWEEP, "sweep kernel", [&] { return pa::launch_sweep(a, r->dshape, r->ctx->cus, r->stream); })))
             return st;
     }
     r->cur = 1 - r->cur;
@@ -857,6 +858,9 @@ pa_status pa_ctx_create(int device, pa_ctx **out) {
     if (se == hipSuccess) (void)pa::static_scratch(device, &se);
     (void)hipSetDevice(prev);
     if (se != hipSuccess) return fail(PA_ERR_DEVICE, std::string("static workspace: ") + hipGetErrorString(se));
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0)
+        return fail(PA_ERR_DEVICE, "cannot query the compute units");
     // the abort word of the team launches: pinned, coherent host memory the
     // kernels poll while they wait at a barrier
     void *abort_word = nullptr;
@@ -869,6 +873,7 @@ pa_status pa_ctx_create(int device, pa_ctx **out) {
         return fail(PA_ERR_NOMEM, "out of host memory");
     }
     c->device = device;
+    c->cus = (uint32_t)cus;
     c->profiling = 0;
     for (auto &x : c->lanes) x = 0;
     c->graphs = 0;
@@ -1108,7 +1113,7 @@ pa_status pa_tune(pa_ctx *ctx, uint32_t L, uint32_t q, uint64_t R, void *d_ws, u
     b.attempts_per_ns = -1.0;
     uint32_t nt = 0;
     for (const auto &c : cands) {
-        if (!pa::quad_fills(L, c.first, c.second, R)) continue;   // its runs would take another shape
+        if (!pa::quad_fills(L, c.first, c.second, R, ctx->cus)) continue;   // its runs would take another shape
         ctx->tune_try_G = c.first;
         ctx->tune_try_wpb = c.second;
         pa_result res{};
@@ -1246,11 +1251,8 @@ pa_status pa_issue_probe(pa_ctx *ctx, uint32_t kind, void *d_out, uint64_t out_b
                          double *lane_instr_per_s) {
     if (!ctx || !d_out || !lane_instr_per_s || kind >= PA_PROBE_KINDS)
         return fail(PA_ERR_INVALID, "bad probe arguments");
-    int cus = 0;
-    if (hipSetDevice(ctx->device) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || cus <= 0)
-        return fail(PA_ERR_DEVICE, "cannot query the compute units");
-    const uint32_t blocks = 8u * (uint32_t)cus;   // 32 waves per compute unit
+    if (hipSetDevice(ctx->device) != hipSuccess) return fail(PA_ERR_DEVICE, "hipSetDevice");
+    const uint32_t blocks = 8u * ctx->cus;   // 32 waves per compute unit
     if (out_bytes < (uint64_t)blocks * pa::probe_threads() * 4u)
         return fail(PA_ERR_NOMEM, "probe output buffer too small");
     const uint32_t iters = kind == PA_PROBE_MIX ? 8192u : 32768u;
@@ -1393,7 +1395,7 @@ pa_status begin_run(pa_ctx *ctx, const pa_run_desc *desc, void *d_ws, uint64_t w
     pa::SweepArgs a = sweep_args(r, 0, mode, nullptr, nullptr, r->at<uint8_t>(p.off_pop[0]), 0);
     const pa::TiledArgs ta = tiled_args(r, 0, nullptr, nullptr, r->at<uint8_t>(p.off_pop[0]));
     auto init = [&]() -> hipError_t {
-        if (!p.tiled) return pa::launch_sweep(a, r->dshape, s);
+        if (!p.tiled) return pa::launch_sweep(a, r->dshape, r->ctx->cus, s);
         const hipError_t e = pa::launch_tiled_init(ta, s);
         return e != hipSuccess ? e : pa::launch_tiled_measure(ta, s);
     };
@@ -1517,7 +1519,7 @@ pa_status pa_run_load(pa_run_state *r, uint32_t step, uint64_t R_cur, const uint
     } else {
         pa::SweepArgs a = sweep_args(r, step, pa::SWEEP_UPDATE, r->at<uint8_t>(p.off_pop[idle]), nullptr,
                                      r->at<uint8_t>(p.off_pop[r->cur]), 0);
-        if ((st = hip_check(r, pa::launch_sweep(a, r->dshape, s), "load kernel"))) return st;
+        if ((st = hip_check(r, pa::launch_sweep(a, r->dshape, r->ctx->cus, s), "load kernel"))) return st;
     }
     if ((st = launch_post_for(r, step)) || (st = hip_check(r, hipStreamSynchronize(s), "sync"))) return st;
     r->dword = r->beyond != 0;
@@ -1967,10 +1969,11 @@ StepLaunch build_step(const std::vector<pa_run_state *> &active, std::vector<uin
     auto shape_key = [](const pa::SweepArgs &a) {
         return ((uint64_t)pa::sweep_class(a.L, a.q, a.T[3] == 0, a.G) << 32) | ((uint64_t)(a.q <= 16) << 8) | a.waves_per_block;
     };
+    const uint32_t cus = active.empty() ? 0u : active[0]->ctx->cus;
     KeySums replicas;
     for (const SW &e : sw) replicas[shape_key(e.a)] += e.a.R_new;
     std::vector<uint32_t> nr;
-    for (SW &e : sw) nr.push_back(pa::settle_sweep(e.a, e.dshape, replicas[shape_key(e.a)]));
+    for (SW &e : sw) nr.push_back(pa::settle_sweep(e.a, e.dshape, replicas[shape_key(e.a)], cus));
     // several replicas per lane in the first runs of a launch, one in the last
     replicas.v.clear();
     for (size_t k = 0; k < sw.size(); ++k)
@@ -1979,7 +1982,7 @@ StepLaunch build_step(const std::vector<pa_run_state *> &active, std::vector<uin
     for (size_t k = sw.size(); k-- > 0;) {
         pa::SweepArgs &a = sw[k].a;
         if (nr[k] > 1) {
-            const uint64_t key = shape_key(a), want = pa::quad_singles(a, nr[k], replicas[key]);
+            const uint64_t key = shape_key(a), want = pa::quad_singles(a, nr[k], replicas[key], cus);
             if (replicas[key] <= want) {
                 nr[k] = 1;
             } else {

@@ -2351,18 +2351,18 @@ bool quad_step(const SweepArgs &a) { return !a.dword && a.q <= 32 && a.T[3] != 0
 //     two kernels differ: 128x128, q = 40, 1024 lanes 1216 attempts/ns, 512
 //     lanes 1281).
 //   - Sides with lane choices: a shape that only the quad kernel has needs a
-//     launch of QUAD_MIN_WAVES, one round of the two 12-wave workgroups a
-//     compute unit holds; below it the dword shape is used (theta = 10, quads /
-//     default shape, attempts per ns: 24x24 766 / 887 with 4000 waves and 1071 /
-//     956 with 8000; 48x48 767 / 865 and 1062 / 984; 96x96 767 / 891 and 1070 /
-//     973).
+//     launch of QUAD_MIN_WAVES per compute unit, one round of the two 12-wave
+//     workgroups it holds; below it the dword shape is used (theta = 10, quads /
+//     default shape, attempts per ns on 256 compute units: 24x24 766 / 887 with
+//     4000 waves and 1071 / 956 with 8000; 48x48 767 / 865 and 1062 / 984; 96x96
+//     767 / 891 and 1070 / 973).
 //   - Other sides: workgroups of fewer waves until there are two per compute
 //     unit.
-constexpr uint64_t QUAD_MIN_WAVES = 6144, QUAD_MIN_BLOCKS = 512;
-bool quad_fills(uint32_t L, uint32_t G, uint32_t waves_per_block, uint64_t replicas) {
-    return quad_any_side(L) || !quad_only(L, G, waves_per_block) || replicas * G / 64u >= QUAD_MIN_WAVES;
+constexpr uint64_t QUAD_MIN_WAVES = 24, QUAD_MIN_BLOCKS = 2;   // per compute unit
+bool quad_fills(uint32_t L, uint32_t G, uint32_t waves_per_block, uint64_t replicas, uint32_t cus) {
+    return quad_any_side(L) || !quad_only(L, G, waves_per_block) || replicas * G / 64u >= QUAD_MIN_WAVES * cus;
 }
-uint32_t settle_sweep(SweepArgs &a, SweepShape dword, uint64_t replicas) {
+uint32_t settle_sweep(SweepArgs &a, SweepShape dword, uint64_t replicas, uint32_t cus) {
     auto max_nr = [&] { return quad_max_nr(a.L, a.q, false, a.G, a.waves_per_block); };
     auto take_dword = [&] {
         a.G = dword.lanes;
@@ -2374,9 +2374,9 @@ uint32_t settle_sweep(SweepArgs &a, SweepShape dword, uint64_t replicas) {
     }
     if (max_nr() != 0 && quad_any_side(a.L)) {
         const uint32_t least = (a.G + 63u) / 64u;
-        while (a.waves_per_block > least && replicas < QUAD_MIN_BLOCKS * (64u * a.waves_per_block / a.G))
+        while (a.waves_per_block > least && replicas < QUAD_MIN_BLOCKS * cus * (64u * a.waves_per_block / a.G))
             a.waves_per_block = (uint16_t)(a.waves_per_block >= least + 4u ? a.waves_per_block - 4u : least);
-    } else if (!quad_fills(a.L, a.G, a.waves_per_block, replicas)) {
+    } else if (!quad_fills(a.L, a.G, a.waves_per_block, replicas, cus)) {
         take_dword();
     }
     return max_nr();
@@ -2384,10 +2384,9 @@ uint32_t settle_sweep(SweepArgs &a, SweepShape dword, uint64_t replicas) {
 
 // (see quad_shape; all of them below two shares, where the long waves would be
 // too few: 32x32, R = 10000 with magnetisation 8415 us a run against 8270)
-uint64_t quad_singles(const SweepArgs &a, uint32_t nr, uint64_t replicas) {
-    constexpr uint64_t CUS = 256;
+uint64_t quad_singles(const SweepArgs &a, uint32_t nr, uint64_t replicas, uint32_t cus) {
     const uint32_t w = a.waves_per_block;
-    const uint64_t slots = CUS * (4u * quad_shape(a.L, a.G).wpe_max / w * w);
+    const uint64_t slots = (uint64_t)cus * (4u * quad_shape(a.L, a.G).wpe_max / w * w);
     const uint64_t share = slots * 64u / a.G * (nr > 2 ? 3u : 4u) / 2u;
     return replicas < 2u * share ? replicas : share;
 }
@@ -2411,11 +2410,11 @@ SweepLaunch sweep_launch(const SweepArgs &a, uint32_t nr) {
     return l;
 }
 
-hipError_t launch_sweep(const SweepArgs &args, SweepShape dword, hipStream_t s) {
+hipError_t launch_sweep(const SweepArgs &args, SweepShape dword, uint32_t cus, hipStream_t s) {
     SweepArgs a = args;
-    uint32_t nr = settle_sweep(a, dword, a.R_new);
+    uint32_t nr = settle_sweep(a, dword, a.R_new, cus);
     if (nr > 1) {
-        const uint64_t singles = quad_singles(a, nr, a.R_new);
+        const uint64_t singles = quad_singles(a, nr, a.R_new, cus);
         if (a.R_new > singles)
             a.big = (uint32_t)((a.R_new - singles) / quad_replicas_per_block(a.G, a.waves_per_block, nr));
         if (a.big == 0) nr = 1;

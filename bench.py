@@ -52,9 +52,10 @@ ALG_OPS_PER_ATTEMPT = 40
 
 # HBM bytes per sweep launch at 128x128, R = 2e5: rocprofv3 FETCH_SIZE x 2.00
 # + WRITE_SIZE x 1.00 (the factors a plain 256 MiB copy gives), average of the
-# step launches 1-3: (2 x 1603274 + 3200009) KiB; 2 R_i N = 6.55e9 bytes are
-# algorithmic (gather + store).
-SWEEP_TRAFFIC_BYTES = (2.0 * 1603274 + 3200009) * 1024
+# step launches 1-3 with the tuned shape: (2 x 1303589 + 3196906) KiB; 2 R_i N =
+# 6.55e9 bytes are algorithmic (gather + store; a lane's two replicas are often
+# copies of one ancestor, which is then read once).
+SWEEP_TRAFFIC_BYTES = (2.0 * 1303589 + 3196906) * 1024
 
 RUN_128 = dict(L=128, q=10, R=200000, K=501, beta_max=1.6, theta=20, seed=4)
 RUN_32 = dict(L=32, q=10, R=20000, K=401, beta_max=1.6, theta=10, seed=2)
@@ -348,9 +349,8 @@ def main():
         print("no GPU visible", file=sys.stderr)
         sys.exit(1)
     pa.lib()
-    # the profiling modes sweep with the default shapes, the others with the
-    # package's tuned shapes (as any Context does)
-    ctx = pa.Context(0, tune_cache=not (args.profile_run or args.profile_steps or args.profile_batch))
+    # (with the package's tuned shapes, the profiling modes too)
+    ctx = pa.Context(0)
     if args.issue_probe:
         print(json.dumps(issue_ceiling(ctx, pa.LIB_PATH)), flush=True)
         return

@@ -185,13 +185,16 @@ pa_status pa_ctx_set_profiling(pa_ctx *ctx, int enable);
  * 48, 96, 192 the sweep kernel exists for one or two lane counts per replica
  * (a divisor of 64: several replicas per wave; a multiple of 64: one replica
  * per workgroup; neither, at L = 12, 20, 24: replicas spanning waves, several
- * per workgroup); results do not depend on the choice.  Other L use one
- * generic shape.  Sides divisible by 8 also have a kernel that updates four
- * sites of a colour per lane (q <= 32, 32-bit thresholds); it runs with the
- * lane counts it has, among them some that the tuned shapes below may name and
- * pa_ctx_get_lanes does not list.  pa_ctx_get_lanes reports the lanes later runs will use and
- * the candidates (0 lanes and no candidates for the tiled path, L > 256);
- * pa_ctx_set_lanes picks one (0 = default) for later runs.
+ * per workgroup); results do not depend on the choice.  Other L have no choice.
+ * Where q <= 32 and the thresholds fit 32 bits, a kernel that updates four
+ * sites of a colour per lane serves L = 8, 16, 24, 32, 48, 64, 96, 128, 192 and
+ * 256, with the lane counts it has there (among them some that the tuned shapes
+ * below may name and pa_ctx_get_lanes does not list), and every even L from 10
+ * to 254 without lane choices, with one shape per L; 12 and 20 have the other
+ * kernel alone.  pa_ctx_get_lanes reports the lanes later runs will use (of L
+ * without lane choices: runs with q <= 32) and the candidates (0 lanes and no
+ * candidates for the tiled path, L > 256); pa_ctx_set_lanes picks one (0 =
+ * default) for later runs.
  * pa_autotune times every candidate on a synthetic population of about 64 MB
  * (K = 3, theta = 4) in the caller's workspace (at least pa_plan's size for
  * it; 256 MB is enough for every L), keeps the fastest in the context and

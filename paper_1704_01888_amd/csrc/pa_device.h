@@ -27,8 +27,10 @@ struct SweepArgs {
     uint32_t theta;
     uint32_t mode;            // SweepMode
     uint32_t key0, key1;      // Philox key
-    uint32_t G;               // lanes per replica: a power of two up to 64 (several replicas
-                              // per wave) or a multiple of 64 (one replica per workgroup)
+    uint32_t G;               // lanes per replica: in the dword kernels a divisor of 64, a
+                              // multiple of 64 (one replica per workgroup) or neither
+                              // (replicas span waves); in the quad kernel any of its shapes',
+                              // with as many replicas per workgroup as fit
     uint16_t waves_per_block;
     uint16_t dword;           // 1: the dword kernel also where the quad kernel has the shape
     uint32_t big;             // quad kernel: the first workgroups, with several replicas per lane

@@ -1944,7 +1944,8 @@ __device__ bool team_barrier(uint32_t *ctr, uint32_t target, const TeamCtl &ctl,
 // A chain of dependent reads in one workgroup: four energies a load, the four
 // weights of a thread read together, and the window, which the answer lies in
 // unless the weights are strongly skewed, in place of the first search steps
-// (post launch of one 8x8 run of R = 1e3: 7.2 -> 6.8 us).
+// (one 8x8 run of R = 1e3 and 200 steps, medians of five processes in turn with
+// the plain form: 3230 -> 3194 us, its post launches 6.9 -> 6.7 us).
 constexpr uint32_t SMALL_WINDOW = 16;
 
 // The resampling into step `st.step` (Sec. 2 step 2, eq. (1)) in one
@@ -2438,7 +2439,8 @@ hipError_t launch_sweep(const SweepArgs &args, SweepShape dword, uint32_t cus, h
 // 15.3 15.9; draws and count scan at 50000 15.5 15.3 15.9 / 16.3 15.9 16.4,
 // 70000 17.2 17.1 18.1 / 17.2 17.1 17.9, 100000 20.1 19.5 20.2 / 18.5 18.3 19.7,
 // 1e6 125.7 129.1 / 93.9 97.0.  The weights of all levels fit LDS, and the
-// blocks' records the scratch.
+// blocks' records the scratch.  Launches of one run only: those of batches and of
+// the server take k_post and the plain count scan at every size.
 bool post_chunks(const PostArgs &a, uint64_t scratch_words) {
     return a.do_weights && a.R_i > CHUNKS_MIN_R && a.nbins <= POST_LDS_BINS / 2u &&
            (uint64_t)scan_blocks(a.R_i, a.wblock) * chunk_stride(a.nbins) <= scratch_words;

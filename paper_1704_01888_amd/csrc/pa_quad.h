@@ -1,7 +1,9 @@
 // pa_quad.h -- the sweep of replicas held in LDS as two colour planes, four
-// sites of one colour per dword ("quads"): q <= 32, lattice sides with a
-// compile-time shape (quad_shape) and, with a shape found by rule (quad_any),
-// every other even side from 8 to 254.
+// sites of one colour per dword ("quads"): q <= 32, the lattice sides 8, 16, 24,
+// 32, 48, 64, 96, 128, 192 and 256 with a shape from a table (quad_shape) and,
+// with a shape found by rule (quad_any), the even sides from 10 to 254 without
+// lane choices.  Sides 12 and 20, whose lane choices have no such shape, and 2,
+// 4 and 6 keep the dword and byte kernels.
 //
 // What bounds it: the issue of vector integer instructions, like the dword
 // kernel (sweeps_fixed), so the layout is chosen to need fewer of them.
@@ -101,6 +103,13 @@ __host__ __device__ constexpr uint32_t quad_rep_bytes(uint32_t L) { return 2u * 
 //     0.92 of the lane time, 8 waves 1053 / 1115 with 0.81),
 //   - 5 % beyond 6 quads per lane, where round 3's half is not kept,
 // and a part where the registers leave fewer than 24 waves on a compute unit.
+// Against the other shapes of a side (16 sides, up to nine shapes each: the next
+// scores, and the best of every workgroup size and number of quads), the rule's
+// rate over the fastest one's: at 30000 replicas (1 GiB from 206 on) 1.00 at 36,
+// 44, 62, 118, 136, 150, 180, 206, 240 and 254, 0.99 at 14, 0.98 at 90, 0.97 at
+// 30 and 72, 0.96 at 80, 0.89 at 22; at 3000 replicas 0.98 to 1.00 from 62 on,
+// and 0.80 to 0.92 at 22, 30, 36 and 44, where such a launch is one partial
+// round and the number of its waves decides.
 struct QuadAny { uint32_t G, waves, wpe; bool hoist; };
 constexpr QuadAny quad_any(uint32_t L) {
     QuadAny best{0, 0, 0, false};

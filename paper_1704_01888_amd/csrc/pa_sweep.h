@@ -68,6 +68,8 @@ __device__ __forceinline__ uint4 philox(uint32_t c0, uint32_t c1, uint32_t c2, u
     return philox_from((uint64_t)PHILOX_M0 * c0, c1, c2, c3, k0, k1);
 }
 
+// Digest term of one dword of a replica: r * d mod 2^64, r the 64-bit word of
+// Philox(n, k, step, DIGEST) made odd (so any change of d changes the term).
 __device__ __forceinline__ uint64_t digest_term(uint32_t n, uint32_t k, uint32_t step, uint32_t d,
                                                 uint32_t key0, uint32_t key1) {
     const uint4 w = philox(n, k, step, DOM_DIGEST << 28, key0, key1);
@@ -88,11 +90,6 @@ __device__ __forceinline__ uint32_t mulhi32_wide(uint32_t w, uint32_t n) {
 __device__ __forceinline__ uint32_t perm(uint32_t hi, uint32_t lo, uint32_t sel) {
     return __builtin_amdgcn_perm(hi, lo, sel);   // byte sel 0-3 from lo, 4-7 from hi
 }
-
-// Digest term of one dword of a replica: r * d mod 2^64, r the 64-bit word of
-// Philox(n, k, step, DIGEST) made odd (so any change of d changes the term).
-__device__ __forceinline__ uint64_t digest_term(uint32_t n, uint32_t k, uint32_t step, uint32_t d,
-                                                uint32_t key0, uint32_t key1);
 
 // Number of equal bytes between two words.
 __device__ __forceinline__ uint32_t eq_bytes(uint32_t a, uint32_t b) {

@@ -345,7 +345,7 @@ pa_status pa_resume(pa_ctx *ctx, const char *path, void *d_ws, uint64_t ws_bytes
  * resampling and init modes) advanced together, one set of segmented launches
  * per global step g for every run with K > g.  The runs start together (one
  * launch of fills and weight-table copies, one initial sweep launch per kernel
- * class, one launch of step-0 statistics) and their per-step results come back
+ * class (small classes of one lattice side share a kernel), one launch of step-0 statistics) and their per-step results come back
  * through one gathering launch and one copy.  Results are identical to n
  * separate pa_run calls.  pa_plan_batch gives the workspace size (the runs'
  * workspaces, the descriptor tables of the start, the steps and the read-back,

@@ -32,7 +32,8 @@ struct SweepArgs {
                               // (replicas span waves); in the quad kernel any of its shapes',
                               // with as many replicas per workgroup as fit
     uint16_t waves_per_block;
-    uint16_t dword;           // 1: the dword kernel also where the quad kernel has the shape
+    uint8_t dword;            // 1: the dword kernel also where the quad kernel has the shape
+    uint8_t wide;             // 1: the quad kernel's form for q <= 32 also where q <= 16
     uint32_t big;             // quad kernel: the first workgroups, with several replicas per lane
 };
 
@@ -220,7 +221,7 @@ hipError_t launch_prep_batch(const PrepRec *recs, const uint32_t *start, uint32_
 
 // Batched forms: several runs per launch.  Sweep launches group runs of one
 // kernel class (sweep_class); `start` [n+1] gives each run's first workgroup.
-uint32_t sweep_class(uint32_t L, uint32_t q, bool t64, uint32_t G, uint32_t nr = 0);
+uint32_t sweep_class(uint32_t L, uint32_t q, bool t64, uint32_t G, uint32_t nr = 0, bool wide = false);
 void *sweep_kernel(uint32_t cls, bool batch);
 hipError_t launch_sweep_batch(uint32_t cls, const SweepArgs *runs, const uint32_t *start, uint32_t n,
                               uint32_t blocks, uint32_t threads, size_t lds, hipStream_t s);
@@ -290,6 +291,13 @@ uint64_t replicas_per_block(uint32_t G, uint32_t waves_per_block);
 // Whether the quad kernel takes a run's step: q <= 32, 32-bit thresholds, no
 // loaded spins beyond q.
 bool quad_step(const SweepArgs &a);
+// Whether it then takes the form for q <= 32 (else that for q <= 16).
+bool quad_wide(const SweepArgs &a);
+// A batch's launches of one side in one (see pa_kernels.hip): the most waves, per
+// compute unit, of runs with q <= 16 that join those above 16, and of runs of the
+// quad kernel (in the dword kernel's shape) that join those of the dword kernel.
+uint64_t quad_join_wide_waves();
+uint64_t quad_join_dword_waves(uint32_t L);
 // Quad kernel (pa_quad.h): the most replicas per lane it has for a run's shape
 // (0: the run does not take it), its lane counts for L (up to 2), whether only
 // it has the shape.

@@ -1864,11 +1864,11 @@ StepLaunch build_step(const std::vector<pa_run_state *> &active, std::vector<uin
     std::vector<uint32_t> sstart, mstart;
     std::vector<pa::SlotmapArgs> sm;
     std::vector<pa::PostArgs> po;
-    struct SW { pa::SweepLaunch l; uint32_t threads; pa::SweepArgs a; const pa_run_state *r; pa::SweepShape dshape; };
+    struct SW { pa::SweepLaunch l; uint32_t threads; pa::SweepArgs a; const pa_run_state *r; };
     std::vector<SW> sw;
     uint32_t sblocks = 0, mblocks = 0;
     const pa_run_state *run = nullptr;
-    auto add_sweep = [&](const pa::SweepArgs &a) { sw.push_back({pa::SweepLaunch{}, 0u, a, run, run->dshape}); };
+    auto add_sweep = [&](const pa::SweepArgs &a) { sw.push_back({pa::SweepLaunch{}, 0u, a, run}); };
     for (pa_run_state *r : active) {
         const Plan &p = r->plan;
         run = r;
@@ -1933,47 +1933,78 @@ StepLaunch build_step(const std::vector<pa_run_state *> &active, std::vector<uin
     std::memcpy(blob.data() + L.sample_start_off, sstart.data(), sstart.size() * 4);
     std::memcpy(blob.data() + L.slot_off, sm.data(), sm.size() * sizeof(pa::SlotmapArgs));
     std::memcpy(blob.data() + L.slot_start_off, mstart.data(), mstart.size() * 4);
-    // Several small runs of one side fill the GPU like one large run: their
-    // shape is the tuned one of the class of their replicas together (20 runs
-    // of 8x8, R = 1000: sweeps of 18.1 us with 8 lanes, 19.1 with 16).
-    struct Side { uint32_t L, cls; uint64_t replicas; bool found, dfound; pa_tune_entry t, d; };
+    // Several small runs of one side fill the GPU like one large run: they take
+    // the quad kernel's shape that is tuned for the class of their replicas
+    // together (20 runs of 8x8, R = 1000: sweeps of 18.1 us with 8 lanes, 19.1 with
+    // the 16 of one run's class).  Other shapes stay the run's own (24x24, 12 runs of
+    // 434: with the dword shape of the class above 1.1 times the time).
+    struct Side { uint32_t L; uint64_t replicas; bool found; pa_tune_entry t; };
     std::vector<Side> sides;
-    auto side_of = [&](const pa::SweepArgs &a) -> Side & {
-        const uint32_t cls = a.q > 128 ? TUNE_LARGE : pa::quad_step(a) ? TUNE_QUAD : TUNE_DWORD;
-        for (Side &d : sides) if (d.L == a.L && d.cls == cls) return d;
-        sides.push_back({a.L, cls, 0u, false, false, {}, {}});
+    auto side_of = [&](uint32_t side) -> Side & {
+        for (Side &d : sides) if (d.L == side) return d;
+        sides.push_back({side, 0u, false, {}});
         return sides.back();
     };
+    auto shared = [](const SW &e) { return e.r->free_shape && pa::quad_step(e.a); };
     for (const SW &e : sw)
-        if (e.r->free_shape) side_of(e.a).replicas += e.a.R_new;
-    for (Side &d : sides) {
-        pa_ctx *ctx = active[0]->ctx;
-        const uint32_t rc = r_class_of(d.replicas);
-        d.found = d.cls == TUNE_QUAD && tune_find(ctx, d.L, TUNE_QUAD, rc, &d.t);
-        d.dfound = tune_find(ctx, d.L, d.cls == TUNE_LARGE ? TUNE_LARGE : TUNE_DWORD, rc, &d.d);
-    }
-    const size_t lds_cap = sides.empty() ? 0 : pa::max_lds_per_block(active[0]->ctx->device);
+        if (shared(e)) side_of(e.a.L).replicas += e.a.R_new;
+    for (Side &d : sides)
+        d.found = tune_find(active[0]->ctx, d.L, TUNE_QUAD, r_class_of(d.replicas), &d.t) &&
+                  pa::quad_max_nr(d.L, 2, false, d.t.lanes, d.t.waves_per_block) != 0;
+    const size_t lds_cap = active.empty() ? 0 : pa::max_lds_per_block(active[0]->ctx->device);
     for (SW &e : sw) {
-        if (!e.r->free_shape) continue;
-        const Side &d = side_of(e.a);
-        if (r_class_of(d.replicas) <= r_class_of(e.r->plan.R_cap)) continue;
-        const uint32_t qc = e.a.Mt_out ? e.a.q : 0u;
-        if (d.found && pa::shape_lds_bytes(e.a.L, e.a.q, d.t.lanes, d.t.waves_per_block, qc) <= lds_cap) {
-            e.a.G = d.t.lanes;
-            e.a.waves_per_block = (uint16_t)d.t.waves_per_block;
-        }
-        if (d.dfound && pa::sweep_lds_bytes(e.a.N, d.d.lanes, d.d.waves_per_block, qc) <= lds_cap)
-            e.dshape = {d.d.lanes, d.d.waves_per_block};
+        if (!shared(e)) continue;
+        const Side &d = side_of(e.a.L);
+        if (!d.found || r_class_of(d.replicas) <= r_class_of(e.r->plan.R_cap) ||
+            pa::shape_lds_bytes(e.a.L, e.a.q, d.t.lanes, d.t.waves_per_block, e.a.Mt_out ? e.a.q : 0u) > lds_cap)
+            continue;
+        e.a.G = d.t.lanes;
+        e.a.waves_per_block = (uint16_t)d.t.waves_per_block;
     }
+    // Small launches of one side are joined, each of which would last as long as
+    // its slowest wave: runs of q <= 16 with those above 16 in one quad launch,
+    // and then the quad kernel's runs with the dword kernel's.
+    const uint32_t cus = active.empty() ? 0u : active[0]->ctx->cus;
+    auto waves = [](uint64_t R, uint32_t G) { return R * G / 64u; };
+    auto form_key = [](const pa::SweepArgs &a) { return ((uint64_t)a.L << 32) | (a.G << 8) | a.waves_per_block; };
+    KeySums narrow, wide;
+    for (const SW &e : sw)
+        if (pa::quad_step(e.a)) (pa::quad_wide(e.a) ? wide : narrow)[form_key(e.a)] += waves(e.a.R_new, e.a.G);
+    for (SW &e : sw)
+        if (pa::quad_step(e.a) && wide[form_key(e.a)] && narrow[form_key(e.a)] <= pa::quad_join_wide_waves() * cus &&
+            pa::shape_lds_bytes(e.a.L, 32, e.a.G, e.a.waves_per_block, e.a.Mt_out ? e.a.q : 0u) <= lds_cap)
+            e.a.wide = 1;
     // the kernels, from all the replicas that runs of one shape bring
     auto shape_key = [](const pa::SweepArgs &a) {
-        return ((uint64_t)pa::sweep_class(a.L, a.q, a.T[3] == 0, a.G) << 32) | ((uint64_t)(a.q <= 16) << 8) | a.waves_per_block;
+        return ((uint64_t)pa::sweep_class(a.L, a.q, a.T[3] == 0, a.G) << 32) | ((uint64_t)pa::quad_wide(a) << 8) | a.waves_per_block;
     };
-    const uint32_t cus = active.empty() ? 0u : active[0]->ctx->cus;
     KeySums replicas;
     for (const SW &e : sw) replicas[shape_key(e.a)] += e.a.R_new;
     std::vector<uint32_t> nr;
-    for (SW &e : sw) nr.push_back(pa::settle_sweep(e.a, e.dshape, replicas[shape_key(e.a)], cus));
+    for (SW &e : sw) nr.push_back(pa::settle_sweep(e.a, e.r->dshape, replicas[shape_key(e.a)], cus));
+    struct Join { uint32_t L, G, wpb; uint64_t waves; };
+    std::vector<Join> joins;
+    auto join_of = [&](uint32_t L) -> Join * {
+        for (Join &j : joins) if (j.L == L) return &j;
+        return nullptr;
+    };
+    for (size_t k = 0; k < sw.size(); ++k) {       // (32-bit thresholds; the byte kernel has one form for all)
+        const pa::SweepArgs &a = sw[k].a;
+        if (nr[k] == 0 && ((a.L & 3u) || (a.q <= 128 && a.T[3] != 0)) && !join_of(a.L))
+            joins.push_back({a.L, a.G, a.waves_per_block, 0u});
+    }
+    for (size_t k = 0; k < sw.size(); ++k)
+        if (Join *j = nr[k] ? join_of(sw[k].a.L) : nullptr) j->waves += waves(sw[k].a.R_new, j->G);
+    for (size_t k = 0; k < sw.size(); ++k) {
+        pa::SweepArgs &a = sw[k].a;
+        const Join *j = nr[k] ? join_of(a.L) : nullptr;
+        if (!j || j->waves > pa::quad_join_dword_waves(a.L) * cus ||
+            pa::sweep_lds_bytes(a.N, j->G, j->wpb, a.Mt_out ? a.q : 0u) > lds_cap)
+            continue;
+        a.G = j->G;
+        a.waves_per_block = (uint16_t)j->wpb;
+        nr[k] = 0;
+    }
     // several replicas per lane in the first runs of a launch, one in the last
     replicas.v.clear();
     for (size_t k = 0; k < sw.size(); ++k)

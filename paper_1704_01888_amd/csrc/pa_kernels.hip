@@ -2344,6 +2344,24 @@ size_t shape_lds_bytes(uint32_t L, uint32_t q, uint32_t G, uint32_t waves_per_bl
 }
 
 bool quad_step(const SweepArgs &a) { return !a.dword && a.q <= 32 && a.T[3] != 0; }
+bool quad_wide(const SweepArgs &a) { return a.wide || a.q > 16 || quad_any_side(a.L); }
+
+// A launch lasts at least as long as one wave's chain and ends in a part-empty
+// round, so that one launch for two kernels' runs saves one of them and costs
+// the difference of the kernels on the runs that change over.  Twelve runs of
+// one side, apart / together:
+//   - q = 8 and 20, the form for q <= 32 being 1 to 3 % slower: 1.05 to 1.31 in
+//     launches of up to two rounds of waves, 1.02 to 1.13 at the largest measured
+//     (24x24, R = 6944 a run; 16x16, 15625), hence eight rounds.
+//   - q = 8, 20 and 40 on sides with lane choices, where the dword kernel takes
+//     1.1 to 1.2 times as long: 64x64 1.57, 1.26, 1.07, 1.01 at R = 61, 122, 244,
+//     488 a run (two rounds of quad runs at 256); 256x256 1.42 at 61; past one round
+//     also 0.93 (192x192, R = 108) to 1.14.
+//   - the generic kernel (1.2 to 1.6 times): 36x36 1.21, 1.09 at R = 192, 385 (below
+//     the line with two of three runs' waves); 100x100 1.21 at 100, 0.97 at 200.
+//   - the byte kernel (1.3 to 2.3 times): 50x50 1.23 at R = 100, 1.03 at 200.
+uint64_t quad_join_wide_waves() { return 256; }
+uint64_t quad_join_dword_waves(uint32_t L) { return L & 3u ? 4u : lane_choice_index(L) < 0 ? 8u : 64u; }
 
 // Settles the kernel of a sweep in a launch that holds `replicas` of its class
 // in all and returns its largest number of replicas per lane (0: not the quad
@@ -2397,10 +2415,10 @@ uint64_t quad_singles(const SweepArgs &a, uint32_t nr, uint64_t replicas, uint32
 SweepLaunch sweep_launch(const SweepArgs &a, uint32_t nr) {
     SweepLaunch l;
     const uint32_t qc = a.Mt_out ? a.q : 0u;
-    l.cls = sweep_class(a.L, a.q, a.T[3] == 0, a.G, nr);
+    l.cls = sweep_class(a.L, a.q, a.T[3] == 0, a.G, nr, quad_wide(a));
     l.per_block = nr ? quad_replicas_per_block(a.G, a.waves_per_block, nr)
                      : replicas_per_block(a.G, a.waves_per_block);
-    l.lds = nr ? quad_lds_bytes(a.L, a.G, a.waves_per_block, nr, a.q, qc)
+    l.lds = nr ? quad_lds_bytes(a.L, a.G, a.waves_per_block, nr, quad_wide(a) ? 32u : 16u, qc)
                : sweep_lds_bytes(a.N, a.G, a.waves_per_block, qc);
     if (nr > 1) {                      // a.big workgroups of nr replicas per lane, then single ones
         const uint64_t one = l.per_block / nr, done = std::min<uint64_t>(a.R_new, a.big * l.per_block);
@@ -2471,10 +2489,10 @@ hipError_t launch_resample(const SampleArgs &a, const SlotmapArgs &m, uint64_t *
 
 // Kernel class: lattice side, lanes per replica, q <= 128, 64-bit thresholds;
 // bit 31 marks the byte kernel of L = 2 (mod 4), bit 30 the quad kernel with
-// log2 of its replicas per lane in bits 28-29 and q > 16 in bit 27.
+// log2 of its replicas per lane in bits 28-29 and its form for q <= 32 in bit 27.
 constexpr uint32_t CLASS_BYTES = 1u << 31, CLASS_QUAD = 1u << 30;
-uint32_t sweep_class(uint32_t L, uint32_t q, bool t64, uint32_t G, uint32_t nr) {
-    if (nr) return CLASS_QUAD | ((nr == 4 ? 2u : nr - 1u) << 28) | ((q > 16 ? 1u : 0u) << 27) | (L << 16) | (G << 2);
+uint32_t sweep_class(uint32_t L, uint32_t q, bool t64, uint32_t G, uint32_t nr, bool wide) {
+    if (nr) return CLASS_QUAD | ((nr == 4 ? 2u : nr - 1u) << 28) | ((wide ? 1u : 0u) << 27) | (L << 16) | (G << 2);
     if (L & 3u) return CLASS_BYTES | (L << 16);
     return (L << 16) | (G << 2) | ((q <= 128) ? 2u : 0u) | (t64 ? 1u : 0u);
 }

@@ -65,6 +65,11 @@ struct PostArgs {
     uint32_t store_hist;      // write the full histograms of step i to hist / mhist
     uint32_t nbins;           // 2N+1
     int32_t two_n;
+    // which workgroups a post launch has (post_blocks): here, so that a workgroup
+    // reads them with the first fields and not with waits of their own
+    uint32_t magnet;          // M~ or the digest is asked for (Mt or H)
+    uint32_t small;           // a population of at most SMALL_RESAMPLE_MAX: one more workgroup does the
+                              // whole resampling into step i+1 (rs) in place of the weight workgroups
     uint64_t R_i;
     uint32_t step;            // i
     uint32_t has_next;        // i + 1 < K
@@ -96,10 +101,7 @@ struct PostArgs {
     uint32_t bin_e, bin_m;    // levels per histogram bin (>= 1)
     uint64_t *fw_e;           // [K][8]: H, jl, jr, h(jl-1), h(jl), h(jr), h(jr+1), unused
     uint64_t *fw_m;           // [K][8], M~ histogram (needs mhist)
-    // a population of at most SMALL_RESAMPLE_MAX: one more workgroup does the
-    // whole resampling into step i+1 (rs) in place of the weight workgroups
-    uint32_t small;
-    SmallResample rs;
+    SmallResample rs;         // (small)
 };
 
 struct SampleArgs {
@@ -139,7 +141,7 @@ __host__ __device__ inline uint32_t scan_blocks(uint64_t n, uint32_t block) { re
 // Workgroups of a post launch: statistics (of the energies; of M~ and the
 // digest, where asked for), the weight blocks, and the resampling workgroup of
 // a small population.
-__host__ __device__ inline uint32_t post_stats_blocks(const PostArgs &a) { return a.Mt || a.H ? 2u : 1u; }
+__host__ __device__ inline uint32_t post_stats_blocks(const PostArgs &a) { return 1u + a.magnet; }
 __host__ __device__ inline uint32_t post_blocks(const PostArgs &a) {
     return post_stats_blocks(a) + (a.do_weights ? scan_blocks(a.R_i, a.wblock) : 0u) + (a.small ? 1u : 0u);
 }

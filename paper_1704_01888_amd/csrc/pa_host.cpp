@@ -545,6 +545,7 @@ pa::PostArgs post_args(pa_run_state *r, uint32_t i) {
     s.C = r->at<uint64_t>(p.off_C);
     s.Mt = p.mag ? r->at<uint32_t>(p.off_Mt) : nullptr;
     s.H = p.digest ? r->at<uint64_t>(p.off_H) : nullptr;
+    s.magnet = s.Mt || s.H ? 1u : 0u;
     s.digest = p.digest ? r->at<uint64_t>(p.off_digest) : nullptr;
     s.mhist = mhist_of(r, i);
     s.q = p.desc.q;

@@ -897,8 +897,10 @@ __device__ SumMinMax block_sum_min_max(int64_t sum, int32_t mn, int32_t mx) {
 // atomics.  sum (of x, not shifted), mn and mx are valid in every thread.
 struct HistBuild { HistView v; int64_t sum; int32_t mn, mx; };
 
+// (forced inline: called, as the compiler chooses once several kernels have it,
+// it takes 0.6 us longer, a tenth of a small population's post launch)
 template <uint32_t V = 32, bool LEAN = false, typename T>
-__device__ HistBuild build_hist(const T *x, uint64_t n, int32_t shift, uint32_t nb, uint32_t *lds,
+__device__ __forceinline__ HistBuild build_hist(const T *x, uint64_t n, int32_t shift, uint32_t nb, uint32_t *lds,
                                 uint32_t cap, uint32_t *out) {
     HistBuild r;
     if (nb <= cap) {
@@ -1379,9 +1381,14 @@ __global__ void __launch_bounds__(WG_THREADS) k_post_chunks(PostArgs a, const ui
 // runs of 8x8, R = 1e3, 11.4 us instead of 8.7).
 __global__ void __launch_bounds__(WG_THREADS) k_post_batch(const PostArgs *__restrict__ runs,
                                                            const uint32_t *start, uint32_t n) {
-    const uint32_t r = segment_of(start, n, blockIdx.x);
+    const uint32_t r = segment_of(start, n, blockIdx.x), b = blockIdx.x - start[r];
     const PostArgs a = runs[r];
-    post_block(a, blockIdx.x - start[r]);
+    // one field of each 64-byte line of the record, read together: the fields that
+    // the branches of post_block read one after the other are then in the scalar
+    // cache (20 runs of 8x8, R = 1e3: 8.4 -> 7.8 us)
+    static_assert(sizeof(PostArgs) <= 5 * 64, "five lines");
+    asm volatile("" ::"s"(a.nbins), "s"(a.do_weights), "s"(a.D), "s"(a.widths), "s"(a.rs.step));
+    post_block(a, b);
 }
 
 // ---------------------------------------------------------------------------
@@ -1944,8 +1951,9 @@ __device__ bool team_barrier(uint32_t *ctr, uint32_t target, const TeamCtl &ctl,
 // A chain of dependent reads in one workgroup: four energies a load, the four
 // weights of a thread read together, and the window, which the answer lies in
 // unless the weights are strongly skewed, in place of the first search steps
-// (one 8x8 run of R = 1e3 and 200 steps, medians of five processes in turn with
-// the plain form: 3230 -> 3194 us, its post launches 6.9 -> 6.7 us).
+// (one 8x8 run of 200 steps, medians of five processes in turn with the plain
+// form: R = 1e3 3230 -> 3150 us, 4e3 4720 -> 4300; its post launches 6.9 -> 6.45 and
+// 13.2 -> 11.1 us).
 constexpr uint32_t SMALL_WINDOW = 16;
 
 // The resampling into step `st.step` (Sec. 2 step 2, eq. (1)) in one
@@ -1966,18 +1974,14 @@ __device__ __forceinline__ void small_resample_body(const SmallResample &st, uin
     }
     // E_ref: the smallest energy (the largest when dbeta < 0)
     int32_t mn = 0x7fffffff, mx = (int32_t)0x80000000;
-    // (four a thread in one load; ru, like E_prev 16-byte aligned, is n rounded
-    // up to a multiple of 4 words)
+    // (four a thread in one load, also where the last ones are past the end: ru and
+    // E_prev, both 16-byte aligned, have room for n rounded up to a multiple of 4.
+    // A load apart for the last thread becomes two round trips for all.)
     for (uint32_t j = 4u * tid; j < n; j += 4u * blockDim.x) {
-        int4 e;
-        if (j + 4u <= n) {
-            e = *reinterpret_cast<const int4 *>(st.E_prev + j);
-        } else {          // the last replica again in place of those past the end
-            e.x = st.E_prev[j];
-            e.y = st.E_prev[min(j + 1u, n - 1u)];
-            e.z = st.E_prev[min(j + 2u, n - 1u)];
-            e.w = e.z;
-        }
+        int4 e = *reinterpret_cast<const int4 *>(st.E_prev + j);
+        e.y = j + 1u < n ? e.y : e.x;
+        e.z = j + 2u < n ? e.z : e.x;
+        e.w = j + 3u < n ? e.w : e.x;
         *reinterpret_cast<int4 *>(ru + j) = e;
         mn = min(min(mn, e.x), min(min(e.y, e.z), e.w));
         mx = max(max(mx, e.x), max(max(e.y, e.z), e.w));

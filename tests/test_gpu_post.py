@@ -85,3 +85,15 @@ def test_small_resampling_with_skewed_weights(ctx, R):
     kw = dict(L=8, q=3, R=R, beta=np.array([0.0, 0.0, 0.5, 1.5, 3.0, 2.0]), theta=1, seed=70 + R, resample=1)
     print(f"\nR={R}", flush=True)
     _compare(pa.pa_run(ctx, pa.Desc(outputs=OUTPUTS[-1] | pa.OUT_FINAL, **kw)), _oracle(kw, OUTPUTS[-1]))
+
+
+@pytest.mark.parametrize("L", [8, 64])
+def test_small_resampling_in_a_batch(ctx, L):
+    """Populations of every remainder of a load of four, each run with a record
+    of its own in one post launch."""
+    runs = [dict(L=L, q=3, R=R, beta=np.array([0.0, 0.0, 0.5, 1.5, 3.0, 2.0]), theta=1, seed=170 + R, resample=R % 2)
+            for R in ((5, 62, 63, 64, 65, 1021, 1024, 2047, 4093, 4094, 4095, 4096) if L == 8 else (30, 31, 33, 200))]
+    print(f"\nL={L}", flush=True)
+    got = pa.pa_run_batch(ctx, [pa.Desc(outputs=OUTPUTS[-1] | pa.OUT_FINAL, **kw) for kw in runs])
+    for g, kw in zip(got, runs):
+        _compare(g, _oracle(kw, OUTPUTS[-1]))

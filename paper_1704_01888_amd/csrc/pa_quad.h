@@ -446,6 +446,12 @@ __device__ __forceinline__ void sweep_quad_body(const SweepArgs &a, uint32_t blo
         }
     };
     auto get4 = [&](uint8_t *rep, uint32_t dd) {
+        if constexpr (Geo::FULL) {       // two bytes from each plane
+            const uint32_t p = dd / (L / 4u) & 1u;
+            const uint32_t e = *reinterpret_cast<const uint16_t *>(rep + p * PB + 2u * dd);
+            const uint32_t o = *reinterpret_cast<const uint16_t *>(rep + (1u - p) * PB + 2u * dd);
+            return perm(o, e, 0x05010400u);
+        }
         uint32_t v = 0;
 #pragma unroll
         for (uint32_t h = 0; h < 2; ++h) {

@@ -2062,14 +2062,24 @@ __device__ __forceinline__ void small_resample_body(const SmallResample &st, uin
         ocarry += total;
     }
     __syncthreads();
-    // the copies of ancestor j fill slots o_j .. o_j + r_j - 1
-    for (uint32_t j = tid; j < n; j += blockDim.x) {
-        const uint32_t r = ru[j], b = o[j];
-        if (ancL)
-            for (uint32_t k = b; k < b + r; ++k) ancL[k] = j;
-        if (write_out) {
-            st.counts_out[j] = r;
-            for (uint32_t k = b; k < b + r; ++k) st.anc_out[k] = j;
+    // the copies of ancestor j fill slots o_j .. o_j + r_j - 1: short runs are
+    // written by their own lane, long ones (strongly skewed weights) by the whole
+    // wave (R = 3e3 in five steps of 0.2 in beta, post launches, the long runs by
+    // single lanes / so: 64x64 57 to 64, by the alignment of their loop / 11.9 us)
+    const auto put = [&](uint32_t k, uint32_t who) {
+        if (ancL) ancL[k] = who;
+        if (write_out) st.anc_out[k] = who;
+    };
+    for (uint32_t j0 = 0; j0 < n; j0 += blockDim.x) {
+        const uint32_t j = j0 + tid;
+        const uint32_t r = j < n ? ru[j] : 0u, b = j < n ? o[j] : 0u;
+        if (write_out && j < n) st.counts_out[j] = r;
+        if (r <= SHORT_RUN)
+            for (uint32_t c = 0; c < r; ++c) put(b + c, j);
+        for (uint64_t todo = __ballot(r > SHORT_RUN); todo; todo &= todo - 1) {
+            const uint32_t src = (uint32_t)__ffsll((unsigned long long)todo) - 1u;
+            const uint32_t start = __shfl(b, src, 64), cnt = __shfl(r, src, 64), who = __shfl(j, src, 64);
+            for (uint32_t c = tid & 63u; c < cnt; c += 64u) put(start + c, who);
         }
     }
     __syncthreads();

@@ -2369,13 +2369,14 @@ bool quad_wide(const SweepArgs &a) { return a.wide || a.q > 16 || quad_any_side(
 //     (24x24, R = 6944 a run; 16x16, 15625), hence eight rounds.
 //   - q = 8, 20 and 40 on sides with lane choices, where the dword kernel takes
 //     1.1 to 1.2 times as long: 64x64 1.57, 1.26, 1.07, 1.01 at R = 61, 122, 244,
-//     488 a run (two rounds of quad runs at 256); 256x256 1.42 at 61; past one round
-//     also 0.93 (192x192, R = 108) to 1.14.
+//     488 a run (two rounds of quad runs at 256), 1.08 for eleven quad runs of
+//     sixteen at 200 (2.2 rounds); 256x256 1.42 at 61; past one round also 0.93
+//     (192x192, R = 108) to 1.14.
 //   - the generic kernel (1.2 to 1.6 times): 36x36 1.21, 1.09 at R = 192, 385 (below
 //     the line with two of three runs' waves); 100x100 1.21 at 100, 0.97 at 200.
 //   - the byte kernel (1.3 to 2.3 times): 50x50 1.23 at R = 100, 1.03 at 200.
 uint64_t quad_join_wide_waves() { return 256; }
-uint64_t quad_join_dword_waves(uint32_t L) { return L & 3u ? 4u : lane_choice_index(L) < 0 ? 8u : 64u; }
+uint64_t quad_join_dword_waves(uint32_t L) { return L & 3u ? 4u : lane_choice_index(L) < 0 ? 8u : 80u; }
 
 // Settles the kernel of a sweep in a launch that holds `replicas` of its class
 // in all and returns its largest number of replicas per lane (0: not the quad

@@ -34,7 +34,7 @@ def _check(ctx, runs, outputs):
 
 
 # populations on both sides of the join with the byte kernel (1024 waves at 10 and
-# 50), the generic one (2048 at 36 and 100) and the table's (16384)
+# 50), the generic one (2048 at 36 and 100) and the table's (20480)
 SIZES = [(10, 21), (10, 1101), (50, 9), (36, 25), (36, 2100), (100, 3), (8, 300), (12, 60), (16, 70), (24, 40), (32, 20),
          (64, 5), (64, 2100), (128, 3), (256, 2)]
 

@@ -446,7 +446,11 @@ __device__ __forceinline__ void sweep_quad_body(const SweepArgs &a, uint32_t blo
         }
     };
     auto get4 = [&](uint8_t *rep, uint32_t dd) {
-        if constexpr (Geo::FULL) {       // two bytes from each plane
+        // (two bytes from each plane, on the sides whose launches the digest
+        // weighs in: 256x256, R = 3e3, theta = 1 1820 -> 1660 us a run of five steps;
+        // at 64x64 nothing, and the batch kernel's sweeps lost 0.8 % with it to
+        // another register allocation)
+        if constexpr (Geo::FULL && L >= 128) {
             const uint32_t p = dd / (L / 4u) & 1u;
             const uint32_t e = *reinterpret_cast<const uint16_t *>(rep + p * PB + 2u * dd);
             const uint32_t o = *reinterpret_cast<const uint16_t *>(rep + (1u - p) * PB + 2u * dd);

@@ -1065,15 +1065,25 @@ static std::vector<std::pair<uint32_t, uint32_t>> tune_candidates(uint32_t L, ui
     return out;
 }
 
-static pa_status tune_check(pa_ctx *ctx, const pa_tune_entry *e) {
-    for (const auto &c : tune_candidates(e->L, tune_class(e->q_large), ctx->device))
+// Whether an entry's shape is one of its side and class.  The shapes of the
+// last side and class asked for stay with the caller: a file has several lines
+// of each.
+struct TuneShapes {
+    uint32_t L = ~0u, cls = ~0u;
+    std::vector<std::pair<uint32_t, uint32_t>> shapes;
+};
+static pa_status tune_check(pa_ctx *ctx, const pa_tune_entry *e, TuneShapes &of) {
+    const uint32_t cls = tune_class(e->q_large);
+    if (of.L != e->L || of.cls != cls) of = {e->L, cls, tune_candidates(e->L, cls, ctx->device)};
+    for (const auto &c : of.shapes)
         if (c.first == e->lanes && c.second == e->waves_per_block) return PA_OK;
     return fail(PA_ERR_INVALID, "not a sweep shape of this lattice side");
 }
 
 pa_status pa_tune_set(pa_ctx *ctx, const pa_tune_entry *e) {
     if (!ctx || !e || e->r_class > 3) return fail(PA_ERR_INVALID, "bad tuned entry");
-    pa_status st = tune_check(ctx, e);
+    TuneShapes of;
+    pa_status st = tune_check(ctx, e, of);
     if (st) return st;
     std::lock_guard<std::mutex> lk(ctx->tune_mu);
     tune_install(ctx, *e);
@@ -1182,24 +1192,21 @@ pa_status pa_tune_save(pa_ctx *ctx, const char *path) {
     return ok ? PA_OK : fail(PA_ERR_INVALID, std::string("cannot write ") + path);
 }
 
-// The value after "key": on a line of the cache file.
-static bool json_field(const std::string &line, const char *key, std::string *out) {
-    const std::string k = std::string("\"") + key + "\"";
-    size_t i = line.find(k);
-    if (i == std::string::npos) return false;
-    i = line.find(':', i + k.size());
-    if (i == std::string::npos) return false;
-    ++i;
-    while (i < line.size() && line[i] == ' ') ++i;
-    size_t j = i;
-    if (j < line.size() && line[j] == '"') {
-        const size_t e = line.find('"', j + 1);
-        if (e == std::string::npos) return false;
-        *out = line.substr(j + 1, e - j - 1);
+// The value after a key, given with its quotes, and a colon on a line of the
+// cache file.
+static bool json_field(const char *line, const char *key, std::string *out) {
+    const char *p = std::strstr(line, key);
+    p = p ? std::strchr(p + std::strlen(key), ':') : nullptr;
+    if (!p) return false;
+    ++p;
+    while (*p == ' ') ++p;
+    if (*p == '"') {
+        const char *e = std::strchr(p + 1, '"');
+        if (!e) return false;
+        out->assign(p + 1, e);
         return true;
     }
-    while (j < line.size() && line[j] != ',' && line[j] != '}') ++j;
-    *out = line.substr(i, j - i);
+    out->assign(p, std::strcspn(p, ",}"));
     return !out->empty();
 }
 
@@ -1209,17 +1216,17 @@ pa_status pa_tune_load(pa_ctx *ctx, const char *path, uint32_t *n_loaded) {
     if (!f) return fail(PA_ERR_INVALID, std::string("cannot read ") + path);
     const std::string arch = ctx_arch(ctx);
     std::vector<pa_tune_entry> got;
+    TuneShapes of;
     char buf[512];
     pa_status st = PA_OK;
     unsigned line_no = 0;
     while (!st && std::fgets(buf, sizeof buf, f)) {
         ++line_no;
-        const std::string line(buf);
-        if (line.find_first_not_of(" \t\r\n") == std::string::npos) continue;
+        if (!buf[std::strspn(buf, " \t\r\n")]) continue;
         std::string a, v[6];
-        const char *keys[6] = {"L", "q_large", "r_class", "lanes", "waves_per_block", "attempts_per_ns"};
-        bool ok = json_field(line, "arch", &a);
-        for (int k = 0; k < 6 && ok; ++k) ok = json_field(line, keys[k], &v[k]);
+        const char *keys[6] = {"\"L\"", "\"q_large\"", "\"r_class\"", "\"lanes\"", "\"waves_per_block\"", "\"attempts_per_ns\""};
+        bool ok = json_field(buf, "\"arch\"", &a);
+        for (int k = 0; k < 6 && ok; ++k) ok = json_field(buf, keys[k], &v[k]);
         if (!ok) {
             st = fail(PA_ERR_INVALID, std::string(path) + ": malformed line " + std::to_string(line_no));
             break;
@@ -1232,7 +1239,7 @@ pa_status pa_tune_load(pa_ctx *ctx, const char *path, uint32_t *n_loaded) {
         e.lanes = (uint32_t)std::strtoul(v[3].c_str(), nullptr, 10);
         e.waves_per_block = (uint32_t)std::strtoul(v[4].c_str(), nullptr, 10);
         e.attempts_per_ns = std::strtod(v[5].c_str(), nullptr);
-        if (e.r_class > 3 || (st = tune_check(ctx, &e)))
+        if (e.r_class > 3 || (st = tune_check(ctx, &e, of)))
             st = fail(PA_ERR_INVALID, std::string(path) + ": line " + std::to_string(line_no) +
                                           " is not a sweep shape of its lattice side");
         else
